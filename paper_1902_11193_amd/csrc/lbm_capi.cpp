@@ -152,6 +152,7 @@ struct lbm_ctx {
     void* nxt;
     lbm::IndexView idx;
     int grid;
+    bool cached;  // the step's results stay in the caches (choose_launch)
     double* partials[2];
     double* ring;
     uint32_t* ctr;      // steps reduced into the ring so far (device, after the ring)
@@ -183,8 +184,8 @@ float scale_of(const lbm_ctx* c) { return std::ldexp(1.0f, c->exponent); }
 // One forward step from `src` to `dst` with partial sums into `partials`;
 // when prev_partials is non-null the same launch reduces them into the next
 // ring slot (the device counter's).
-hipError_t step_raw(lbm_ctx* c, const void* src, void* dst, double* partials,
-                    const double* prev_partials = nullptr, hipStream_t stream = nullptr) {
+hipError_t step_raw(lbm_ctx* c, const void* src, void* dst, double* partials, const double* prev_partials,
+                    hipStream_t stream, bool cached) {
     lbm::StepLaunch a{};
     a.storage = c->storage;
     a.collision = c->collision;
@@ -203,12 +204,13 @@ hipError_t step_raw(lbm_ctx* c, const void* src, void* dst, double* partials,
     a.field = c->field;
     a.scale = scale_of(c);
     a.inv_scale = 1.0f / a.scale;
+    a.cached = cached;
     a.grid = c->grid;
     a.partials = partials;
     a.prev_partials = prev_partials;
     a.ring = c->ring;
     a.ctr = c->ctr;
-    return lbm::launch_step(a, stream ? stream : c->stream);
+    return lbm::launch_step(a, stream);
 }
 
 void drop_graphs(lbm_ctx* c) {
@@ -238,7 +240,7 @@ hipGraphExec_t graph_for(lbm_ctx* c) {
     hipError_t he = hipSuccess;
     for (int k = 0; k < kGraphSteps && he == hipSuccess; ++k) {
         const int64_t t = c->steps + k;
-        he = step_raw(c, cur, nxt, c->partials[t & 1], c->partials[(t - 1) & 1], c->cap_stream);
+        he = step_raw(c, cur, nxt, c->partials[t & 1], c->partials[(t - 1) & 1], c->cap_stream, c->cached);
         std::swap(cur, nxt);
     }
     hipGraph_t graph = nullptr;
@@ -255,23 +257,50 @@ hipGraphExec_t graph_for(lbm_ctx* c) {
     return exec;
 }
 
-// One resident wave of blocks: every block starts at once and walks the
-// chunk list with stride `grid` (a multiple of the XCD count when >= 64),
-// so the chunks in flight form a window of `grid` consecutive chunks.  With
-// FP32 storage one block per compute unit: that step is bound by the L2
-// misses of its gathers, not by latency, and the narrowest window serves
-// them best (512^3 rock: 0.833 ms with 5 blocks per unit, 0.827 with 2,
-// 0.769 with 1).  The 16-bit storages, bound by the loads they can keep in
-// flight, take every block that fits (1 per unit: FP16 0.575 -> 0.670 ms).
-hipError_t choose_grid(lbm_ctx* c) {
+// Bytes a step goes over: both states, the neighbour index and, with
+// full-way bounce-back, the delay line.
+size_t index_bytes(const lbm_ctx* c) { return c->L.partials - std::max(c->L.table, c->L.coords); }
+size_t step_bytes(const lbm_ctx* c) {
+    size_t b = 2 * state_bytes(c->storage, c->np) + index_bytes(c);
+    if (c->wall_mode == LBM_WALL_FULLWAY) b += (size_t)19 * c->np * 4;
+    return b;
+}
+// Bytes a reverse step of the adjoint goes over: two adjoint states, a forward
+// state, the FP32 force sensitivities and the index.
+size_t adjoint_bytes(const lbm_ctx* c) {
+    return (size_t)(3 * 19 + 3) * 4 * c->np + index_bytes(c);
+}
+
+// The launch shape of a step: every block starts at once and walks the chunk
+// list with stride `grid`, so the chunks in flight form a window of `grid`
+// consecutive chunks.
+//
+// Stores: where all a step goes over fits the 256 MB cache behind L2, plain
+// stores leave the results there for the next step; past it they only push
+// out what is still to be read, and streaming stores win.  (Porosity-0.2
+// rocks, us per step cached / streaming: FP32 128^3 17.0 / 19.2, 200^3, 257 MB
+// with its index, 47.5 / 51.5, 208^3, 290 MB, 64.1 / 56.9; FP16 240^3, 234 MB,
+// 52.9 / 62.9, 256^3, 284 MB, 78.6 / 74.7.)
+//
+// Blocks: an image whose chunks all fit takes one block per chunk.  Beyond
+// that the 16-bit storages, bound by the loads they can keep in flight, take
+// every block that fits (512^3 rock, 1 per unit: FP16 0.575 -> 0.670 ms).
+// FP32 storage takes two per compute unit while the step runs out of the
+// cache (1 / 2 / 3 per unit: 128^3 19.4 / 17.0 / 17.3 us, 160^3, 132 MB, 28.8
+// / 27.5 / 27.0, 180^3, 187 MB, 36.4 / 36.7 / 36.1) and one from HBM, where
+// the narrowest window keeps to the fewest DRAM pages (512^3 0.738 / 0.840 ms).
+constexpr size_t kCacheBytes = (size_t)256 << 20;
+constexpr size_t kTwoBlockBytes = (size_t)160 << 20;
+hipError_t choose_launch(lbm_ctx* c) {
     int per_cu = 0;
     hipError_t he = lbm::step_occupancy(c->storage, c->index_kind, c->collision, &per_cu);
     if (he != hipSuccess) return he;
-    if (c->storage == LBM_F32) per_cu = 1;
-    const int64_t chunks = (c->nf + 255) / 256;
-    int64_t G = std::min<int64_t>(chunks, (int64_t)std::max(c->cus, 1) * std::max(per_cu, 1));
-    if (G >= 64) G -= G % 8;
-    c->grid = (int)std::min<int64_t>(G, kMaxGrid);
+    per_cu = std::max(per_cu, 1);
+    const int64_t cus = std::max(c->cus, 1), chunks = c->np / lbm::kChunk;
+    const size_t bytes = step_bytes(c);
+    if (c->storage == LBM_F32 && chunks > cus * per_cu) per_cu = bytes <= kTwoBlockBytes ? std::min(per_cu, 2) : 1;
+    c->grid = (int)std::min<int64_t>({chunks, cus * per_cu, (int64_t)kMaxGrid});
+    c->cached = bytes <= kCacheBytes;
     return hipSuccess;
 }
 
@@ -300,7 +329,7 @@ int do_steps(lbm_ctx* c, int n) {
         }
         const int64_t t = c->steps;
         const double* prev = c->pending ? c->partials[(t - 1) & 1] : nullptr;
-        HIP_TRY(step_raw(c, c->cur, c->nxt, c->partials[t & 1], prev));
+        HIP_TRY(step_raw(c, c->cur, c->nxt, c->partials[t & 1], prev, c->stream, c->cached));
         std::swap(c->cur, c->nxt);
         ++c->steps;
         c->pending = true;
@@ -568,7 +597,7 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
     hipError_t he = hipGetDevice(&dev);
     if (he == hipSuccess) he = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (he != hipSuccess) return cleanup(fail(LBM_EHIP, std::string("device query: ") + hipGetErrorString(he)));
-    he = choose_grid(c);
+    he = choose_launch(c);
     if (he != hipSuccess) return cleanup(fail(LBM_EHIP, std::string("occupancy query: ") + hipGetErrorString(he)));
 
     lbm::IndexView& v = c->idx;
@@ -882,13 +911,12 @@ int lbm_set_collision(lbm_ctx* c, int collision) {
         int rc = flush(c);  // the pending partials were written with the current grid
         if (rc) return rc;
     }
-    const int old = c->collision, old_grid = c->grid;
+    const int old = c->collision;
     c->collision = collision;
     drop_graphs(c);
-    hipError_t he = choose_grid(c);
+    hipError_t he = choose_launch(c);
     if (he != hipSuccess) {
         c->collision = old;
-        c->grid = old_grid;
         return fail(LBM_EHIP, std::string("occupancy query: ") + hipGetErrorString(he));
     }
     return LBM_OK;
@@ -903,9 +931,12 @@ int lbm_wall_workspace_query(lbm_ctx* c, size_t* bytes) {
 int lbm_set_wall(lbm_ctx* c, int mode, void* workspace, size_t workspace_bytes) {
     if (!c) return fail(LBM_EINVAL, "ctx is NULL");
     if (mode == LBM_WALL_HALFWAY) {
+        int rc = flush(c);  // the pending partials were written with the current grid
+        if (rc) return rc;
         c->wall_mode = mode;
         c->wallbuf = nullptr;
         drop_graphs(c);
+        HIP_TRY(choose_launch(c));
         return LBM_OK;
     }
     if (mode != LBM_WALL_FULLWAY) return fail(LBM_EINVAL, "mode must be LBM_WALL_HALFWAY or LBM_WALL_FULLWAY");
@@ -914,11 +945,14 @@ int lbm_set_wall(lbm_ctx* c, int mode, void* workspace, size_t workspace_bytes) 
     const size_t need = align256((size_t)19 * c->np * 4);
     if (!workspace || ((uintptr_t)workspace & 255)) return fail(LBM_EWORKSPACE, "wall workspace NULL or not 256-byte aligned");
     if (workspace_bytes < need) return fail(LBM_EWORKSPACE, "wall workspace too small: need " + std::to_string(need));
+    int rc = flush(c);
+    if (rc) return rc;
     c->wallbuf = static_cast<float*>(workspace);
     // the state one step older than the current one starts equal to it
     HIP_TRY(hipMemcpyAsync(c->wallbuf, c->cur, (size_t)19 * c->np * 4, hipMemcpyDeviceToDevice, c->stream));
     c->wall_mode = mode;
     drop_graphs(c);
+    HIP_TRY(choose_launch(c));
     return LBM_OK;
 }
 
@@ -1116,7 +1150,13 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     al.field = c->field;
     al.dk_acc = (float*)(ws + A.acc);
     al.acc_stride = c->np;
-    al.grid = c->grid;
+    // As for the steps (choose_launch), by what a reverse step goes over: cached
+    // stores and two blocks per compute unit inside the 256 MB cache, streaming
+    // stores and one from HBM (us per adjoint step, 1 / 2 blocks: 128^3 rock,
+    // cached 63.1 / 58.3, streaming 64.3 / 62.5; 160^3, 206 MB, 103.2 / 100.5
+    // and 103.8 / 104.3; 192^3, 350 MB, 168.5 / 171.0 and 162.7 / 165.8).
+    al.cached = adjoint_bytes(c) <= kCacheBytes;
+    al.grid = (int)std::min<int64_t>(c->np / lbm::kChunk, (int64_t)std::max(c->cus, 1) * (al.cached ? 2 : 1));
     al.partials = part6;
     const int nrev = N - 1;  // reverse steps n = N-1 .. 1
     for (int s = (nrev + K - 1) / K - 1; s >= 0; --s) {
@@ -1126,7 +1166,7 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
         HIP_TRY(timer.mark(kPhaseRecompute, c->stream));
         for (int t = 1; t < n1 - n0; ++t) {
             const void* src = t == 1 ? (const void*)snap(s) : (const void*)seg(t - 1);
-            HIP_TRY(step_raw(c, src, seg(t), scratch4));
+            HIP_TRY(step_raw(c, src, seg(t), scratch4, nullptr, c->stream, al.cached));
         }
         HIP_TRY(timer.mark(kPhaseReverse, c->stream));
         for (int n = n1; n > n0; --n) {
@@ -1145,7 +1185,7 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     double dv[3] = {0, 0, 0};
     dv[c->axis] = nu / (2.0 * gref * V);
     HIP_TRY(lbm::launch_add_uniform(dk_dg, c->nf, dv[0], dv[1], dv[2], c->stream));
-    HIP_TRY(lbm::launch_finalize6(part6, c->grid, out6, c->stream));
+    HIP_TRY(lbm::launch_finalize6(part6, al.grid, out6, c->stream));
     double cls[6];
     HIP_TRY(hipMemcpyAsync(cls, out6, sizeof(cls), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));

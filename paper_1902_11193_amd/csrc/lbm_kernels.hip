@@ -123,12 +123,24 @@ template <class T>
 __device__ __forceinline__ void st_off(T* base, uint32_t byte_off, T v) {
     *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off) = v;
 }
-// Streaming store: the next step reads these values only after the whole
-// population array (gigabytes) has gone through the caches, so they are
-// written without displacing cached lines the gathers still reuse.
+// Streaming store, for states larger than the caches: the next step reads
+// these values only after the whole population array (gigabytes) has gone
+// through the caches, so they are written without displacing cached lines
+// the gathers still reuse.
 template <class T>
 __device__ __forceinline__ void st_stream(T* base, uint32_t byte_off, T v) {
     __builtin_nontemporal_store(v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off));
+}
+
+// Store of a node's result: CACHED where the states fit the caches (the next
+// step reads them there), else streaming.  Which of the two a launch takes
+// follows from the size of the states (kCachedBytes).
+template <bool CACHED, class T>
+__device__ __forceinline__ void st_state(T* base, uint32_t byte_off, T v) {
+    if constexpr (CACHED)
+        st_off(base, byte_off, v);
+    else
+        st_stream(base, byte_off, v);
 }
 
 // ------------------------------------------------------------------ layout
@@ -936,7 +948,7 @@ k_finalize_ring(const double* __restrict__ partials, int grid, double* __restric
 // CU, which the 16-bit storages use (FP32 storage launches one block per CU);
 // the reference-density, link-wise TRT, full-way and symmetry variants would
 // spill there and keep the compiler's choice.
-template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH = false, bool SYM = false>
+template <class C, class Ix, bool CACHED, bool FIELD, bool TRT, bool FW, bool ZH = false, bool SYM = false>
 __global__ void __launch_bounds__(kThreads, (C::kRef || TRT || FW || SYM) ? 1 : 5)
 k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, Ix ix,
        uint32_t slack, uint32_t nf, RatesF r, float Fx0, float Fy0, float Fz0,
@@ -1089,15 +1101,15 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
                 // collision conserves, rounded to the stored type
                 const T r_new = (T)drho;
                 const float rf = (float)r_new;
-                st_stream(rdst + (size_t)c * kThreads, so, r_new);
+                st_state<CACHED>(rdst + (size_t)c * kThreads, so, r_new);
                 unroll<19>([&](auto k) {
                     constexpr int i = decltype(k)::value;
-                    st_stream(db + i * kThreads, so, C::enc(f[i] - wgt(i) * rf, scale));
+                    st_state<CACHED>(db + i * kThreads, so, C::enc(f[i] - wgt(i) * rf, scale));
                 });
             } else {
                 unroll<19>([&](auto k) {
                     constexpr int i = decltype(k)::value;
-                    st_stream(db + i * kThreads, so, C::enc(f[i], scale));
+                    st_state<CACHED>(db + i * kThreads, so, C::enc(f[i], scale));
                 });
             }
             c += G;
@@ -1158,7 +1170,7 @@ __device__ __forceinline__ Vec3 gquad(float vx, float vy, float vz, const Mom& w
 // latency), where the registers this pipeline needs (151) cost no occupancy.
 // Tail lanes as in k_step: lanes past the list load node nf - 1 and store to
 // their own padded slots.
-template <class Ix, bool FIELD>
+template <class Ix, bool CACHED, bool FIELD>
 __global__ void __launch_bounds__(kThreads)
 k_adjoint(const float* __restrict__ ain, float* __restrict__ aout, const float* __restrict__ st,
           Ix ix, uint32_t slack, uint32_t nf, RatesF r, float Fx0, float Fy0, float Fz0,
@@ -1306,7 +1318,7 @@ k_adjoint(const float* __restrict__ ain, float* __restrict__ aout, const float* 
             float* ob_ = aout + (size_t)c * kChunkElems;
             unroll<19>([&](auto k) {
                 constexpr int i = decltype(k)::value;
-                st_stream(ob_ + i * kThreads, threadIdx.x * 4u, b[i]);
+                st_state<CACHED>(ob_ + i * kThreads, threadIdx.x * 4u, b[i]);
             });
             c += G;
             if (c >= chunks) break;
@@ -1365,40 +1377,37 @@ BitmapIdx bitmap_view(const IndexView& v) {
                      mz ? 0u : wrap, mz ? 0u : 0u - wrap, (uint32_t)v.sym};
 }
 
+template <class C, class Ix, bool CACHED, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
+hipError_t step_kernel(const StepLaunch& a, Ix ix, hipStream_t s) {
+    using T = typename C::T;
+    hipLaunchKernelGGL((k_step<C, Ix, CACHED, FIELD, TRT, FW, ZH, SYM>), dim3(a.grid), dim3(kThreads), 0, s,
+                       static_cast<const T*>(a.src), static_cast<T*>(a.dst), ix, (uint32_t)a.idx.slack,
+                       (uint32_t)a.nf, a.rates, a.F[0], a.F[1], a.F[2], FIELD ? a.field : nullptr, a.scale,
+                       a.inv_scale, a.partials, a.prev_partials, a.ring, a.ctr, FW ? a.wall : nullptr,
+                       ZH ? a.drho_in : 0.f, ZH ? a.drho_out : 0.f);
+    return hipGetLastError();
+}
+template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
+hipError_t step_stores(const StepLaunch& a, Ix ix, hipStream_t s) {
+    if (a.cached) return step_kernel<C, Ix, true, FIELD, TRT, FW, ZH, SYM>(a, ix, s);
+    return step_kernel<C, Ix, false, FIELD, TRT, FW, ZH, SYM>(a, ix, s);
+}
 template <class C, class Ix, bool TRT, bool FW, bool SYM = false>
 hipError_t step_launch(const StepLaunch& a, Ix ix, hipStream_t s) {
-    using T = typename C::T;
-    const T* src = static_cast<const T*>(a.src);
-    T* dst = static_cast<T*>(a.dst);
-    if (a.field)
-        hipLaunchKernelGGL((k_step<C, Ix, true, TRT, FW, false, SYM>), dim3(a.grid), dim3(kThreads), 0, s, src, dst,
-                           ix, (uint32_t)a.idx.slack, (uint32_t)a.nf, a.rates, a.F[0], a.F[1], a.F[2], a.field,
-                           a.scale, a.inv_scale, a.partials, a.prev_partials, a.ring, a.ctr, a.wall, 0.f, 0.f);
-    else
-        hipLaunchKernelGGL((k_step<C, Ix, false, TRT, FW, false, SYM>), dim3(a.grid), dim3(kThreads), 0, s, src,
-                           dst, ix, (uint32_t)a.idx.slack, (uint32_t)a.nf, a.rates, a.F[0], a.F[1], a.F[2], nullptr,
-                           a.scale, a.inv_scale, a.partials, a.prev_partials, a.ring, a.ctr, a.wall, 0.f, 0.f);
-    return hipGetLastError();
+    if (a.field) return step_stores<C, Ix, true, TRT, FW, false, SYM>(a, ix, s);
+    return step_stores<C, Ix, false, TRT, FW, false, SYM>(a, ix, s);
 }
 
-// Zou-He pressure faces: FP32 storage, bitmap index, uniform (zero) force,
-// halfway bounce-back.
-template <bool TRT>
-hipError_t step_pressure(const StepLaunch& a, BitmapIdx ix, hipStream_t s) {
-    hipLaunchKernelGGL((k_step<CodecF32, BitmapIdx, false, TRT, false, true>), dim3(a.grid), dim3(kThreads), 0, s,
-                       static_cast<const float*>(a.src), static_cast<float*>(a.dst), ix, (uint32_t)a.idx.slack,
-                       (uint32_t)a.nf, a.rates, a.F[0], a.F[1], a.F[2], nullptr, a.scale, a.inv_scale, a.partials,
-                       a.prev_partials, a.ring, a.ctr, nullptr, a.drho_in, a.drho_out);
-    return hipGetLastError();
-}
-
-// Full-way bounce-back is built for FP32 storage only; symmetry planes for
-// FP32 storage and the bitmap index, without pressure faces.
+// Zou-He pressure faces are built for FP32 storage, the bitmap index, a
+// uniform (zero) force and halfway bounce-back; full-way bounce-back for FP32
+// storage; symmetry planes for FP32 storage and the bitmap index, without
+// pressure faces.
 template <class C, class Ix, bool TRT>
 hipError_t step_with(const StepLaunch& a, Ix ix, hipStream_t s) {
     if (a.pressure) {
         if constexpr (std::is_same<C, CodecF32>::value && std::is_same<Ix, BitmapIdx>::value) {
-            if (!a.wall && !a.field && !a.idx.sym) return step_pressure<TRT>(a, ix, s);
+            if (!a.wall && !a.field && !a.idx.sym)
+                return step_stores<C, Ix, false, TRT, false, true, false>(a, ix, s);
         }
         return hipErrorInvalidValue;
     }
@@ -1434,19 +1443,18 @@ hipError_t step_collision(const StepLaunch& a, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
+template <class Ix, bool CACHED, bool FIELD>
+hipError_t adjoint_kernel(const AdjLaunch& a, Ix ix, hipStream_t s) {
+    hipLaunchKernelGGL((k_adjoint<Ix, CACHED, FIELD>), dim3(a.grid), dim3(kThreads), 0, s, a.adj_in, a.adj_out,
+                       a.state, ix, (uint32_t)a.idx.slack, (uint32_t)a.nf, a.rates, a.F[0], a.F[1], a.F[2],
+                       FIELD ? a.field : nullptr, a.dk_acc, (uint32_t)a.acc_stride, (int)a.first, a.partials);
+    return hipGetLastError();
+}
 template <class Ix>
 hipError_t adjoint_with(const AdjLaunch& a, Ix ix, hipStream_t s) {
-    if (a.field)
-        hipLaunchKernelGGL((k_adjoint<Ix, true>), dim3(a.grid), dim3(kThreads), 0, s, a.adj_in,
-                           a.adj_out, a.state, ix, (uint32_t)a.idx.slack, (uint32_t)a.nf, a.rates,
-                           a.F[0], a.F[1], a.F[2], a.field, a.dk_acc, (uint32_t)a.acc_stride, (int)a.first,
-                           a.partials);
-    else
-        hipLaunchKernelGGL((k_adjoint<Ix, false>), dim3(a.grid), dim3(kThreads), 0, s, a.adj_in,
-                           a.adj_out, a.state, ix, (uint32_t)a.idx.slack, (uint32_t)a.nf, a.rates,
-                           a.F[0], a.F[1], a.F[2], nullptr, a.dk_acc, (uint32_t)a.acc_stride, (int)a.first,
-                           a.partials);
-    return hipGetLastError();
+    if (a.cached)
+        return a.field ? adjoint_kernel<Ix, true, true>(a, ix, s) : adjoint_kernel<Ix, true, false>(a, ix, s);
+    return a.field ? adjoint_kernel<Ix, false, true>(a, ix, s) : adjoint_kernel<Ix, false, false>(a, ix, s);
 }
 
 }  // namespace
@@ -1478,7 +1486,7 @@ hipError_t step_occupancy(int storage, int index_kind, int collision, int* block
     auto q = [&](const void* k) {
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, kThreads, 0);
     };
-#define LBM_OCC(C, I, R) q(reinterpret_cast<const void*>(&k_step<C, I, false, R, false>))
+#define LBM_OCC(C, I, R) q(reinterpret_cast<const void*>(&k_step<C, I, false, false, R, false>))
 #define LBM_OCC2(R)                                                     \
     if (index_kind == kTable) {                                         \
         if (storage == kF32) return LBM_OCC(CodecF32, TableIdx, R);     \

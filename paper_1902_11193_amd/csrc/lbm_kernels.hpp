@@ -57,6 +57,7 @@ struct StepLaunch {
     float F[3];           // uniform force density
     const float* field;   // optional [3][nf] accelerations (rho0 = 1), or nullptr
     float scale, inv_scale;
+    bool cached;          // results stay in the caches for the next step (else streaming stores)
     int grid;             // number of blocks (fixed per context)
     double* partials;     // [grid][4] written by this step
     const double* prev_partials;  // [grid][4] of the previous step, reduced by block 0 into
@@ -99,6 +100,7 @@ struct AdjLaunch {
                            // written by the step with `first`, added to by the others
     int64_t acc_stride;    // >= padded node count
     bool first;
+    bool cached;           // a^n stays in the caches for the next step (else streaming stores)
     int grid;
     double* partials;      // [grid][6] accumulated in place: rate-class sensitivities
 };
