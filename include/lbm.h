@@ -315,8 +315,9 @@ int lbm_set_collision(lbm_ctx* ctx, int collision);
 /* Host + enqueue.  Chooses the wall scheme for the following steps.
  * LBM_WALL_FULLWAY needs FP32 storage and a device workspace of
  * lbm_wall_workspace_query bytes (256-byte aligned, caller-owned, must outlive
- * the mode): it holds every node's populations of one step earlier, and is
- * initialised to the current state (as is again by lbm_set_state).
+ * the mode).  The populations of one step earlier that it takes start equal to
+ * the current state (as again after lbm_set_state); they are read from the
+ * state buffer a step overwrites, so the workspace itself is not written.
  * LBM_WALL_HALFWAY releases it (workspace may be NULL).  Errors: LBM_EINVAL
  * (unknown mode, storage other than FP32), LBM_EWORKSPACE.  lbm_adjoint refuses a
  * context in full-way mode. */

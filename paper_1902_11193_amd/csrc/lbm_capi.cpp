@@ -138,7 +138,6 @@ struct lbm_ctx {
     int storage, index_kind;
     int collision;
     int wall_mode;      // LBM_WALL_HALFWAY or LBM_WALL_FULLWAY
-    float* wallbuf;     // full-way delay line (caller's workspace), state layout
     bool pressure;      // Zou-He pressure faces on x = 0 and x = nx - 1
     double rho_in, rho_out;
     int cus;
@@ -189,7 +188,7 @@ hipError_t step_raw(lbm_ctx* c, const void* src, void* dst, double* partials, co
     lbm::StepLaunch a{};
     a.storage = c->storage;
     a.collision = c->collision;
-    a.wall = c->wall_mode == LBM_WALL_FULLWAY ? c->wallbuf : nullptr;
+    a.fullway = c->wall_mode == LBM_WALL_FULLWAY;
     a.pressure = c->pressure;
     a.drho_in = (float)(c->rho_in - 1.0);
     a.drho_out = (float)(c->rho_out - 1.0);
@@ -257,13 +256,10 @@ hipGraphExec_t graph_for(lbm_ctx* c) {
     return exec;
 }
 
-// Bytes a step goes over: both states, the neighbour index and, with
-// full-way bounce-back, the delay line.
+// Bytes a step goes over: both states and the neighbour index.
 size_t index_bytes(const lbm_ctx* c) { return c->L.partials - std::max(c->L.table, c->L.coords); }
 size_t step_bytes(const lbm_ctx* c) {
-    size_t b = 2 * state_bytes(c->storage, c->np) + index_bytes(c);
-    if (c->wall_mode == LBM_WALL_FULLWAY) b += (size_t)19 * c->np * 4;
-    return b;
+    return 2 * state_bytes(c->storage, c->np) + index_bytes(c);
 }
 // Bytes a reverse step of the adjoint goes over: two adjoint states, a forward
 // state, the FP32 force sensitivities and the index.
@@ -578,7 +574,6 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
 
     c->collision = LBM_COLLIDE_MRT;
     c->wall_mode = LBM_WALL_HALFWAY;
-    c->wallbuf = nullptr;
     c->pressure = false;
     c->rho_in = c->rho_out = 1.0;
     c->cus = 0;
@@ -879,7 +874,7 @@ int lbm_set_state(lbm_ctx* c, const double* f) {
     }
     HIP_TRY(hipMemcpyAsync(c->cur, raw.data(), raw.size(), hipMemcpyHostToDevice, c->stream));
     if (c->wall_mode == LBM_WALL_FULLWAY)  // the state one step older starts equal to it
-        HIP_TRY(hipMemcpyAsync(c->wallbuf, c->cur, raw.size(), hipMemcpyDeviceToDevice, c->stream));
+        HIP_TRY(hipMemcpyAsync(c->nxt, c->cur, raw.size(), hipMemcpyDeviceToDevice, c->stream));
     HIP_TRY(zero_ring(c));
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->steps = 0;
@@ -931,12 +926,8 @@ int lbm_wall_workspace_query(lbm_ctx* c, size_t* bytes) {
 int lbm_set_wall(lbm_ctx* c, int mode, void* workspace, size_t workspace_bytes) {
     if (!c) return fail(LBM_EINVAL, "ctx is NULL");
     if (mode == LBM_WALL_HALFWAY) {
-        int rc = flush(c);  // the pending partials were written with the current grid
-        if (rc) return rc;
         c->wall_mode = mode;
-        c->wallbuf = nullptr;
         drop_graphs(c);
-        HIP_TRY(choose_launch(c));
         return LBM_OK;
     }
     if (mode != LBM_WALL_FULLWAY) return fail(LBM_EINVAL, "mode must be LBM_WALL_HALFWAY or LBM_WALL_FULLWAY");
@@ -945,14 +936,11 @@ int lbm_set_wall(lbm_ctx* c, int mode, void* workspace, size_t workspace_bytes) 
     const size_t need = align256((size_t)19 * c->np * 4);
     if (!workspace || ((uintptr_t)workspace & 255)) return fail(LBM_EWORKSPACE, "wall workspace NULL or not 256-byte aligned");
     if (workspace_bytes < need) return fail(LBM_EWORKSPACE, "wall workspace too small: need " + std::to_string(need));
-    int rc = flush(c);
-    if (rc) return rc;
-    c->wallbuf = static_cast<float*>(workspace);
-    // the state one step older than the current one starts equal to it
-    HIP_TRY(hipMemcpyAsync(c->wallbuf, c->cur, (size_t)19 * c->np * 4, hipMemcpyDeviceToDevice, c->stream));
+    // the state one step older than the current one starts equal to it; it is
+    // read from the buffer the next step overwrites
+    HIP_TRY(hipMemcpyAsync(c->nxt, c->cur, (size_t)19 * c->np * 4, hipMemcpyDeviceToDevice, c->stream));
     c->wall_mode = mode;
     drop_graphs(c);
-    HIP_TRY(choose_launch(c));
     return LBM_OK;
 }
 

@@ -64,8 +64,7 @@ struct StepLaunch {
                                   // ring slot (*ctr % kRingSlots), then ++*ctr; nullptr: nothing pending
     double* ring;                 // [kRingSlots][4] per-step sums
     uint32_t* ctr;                // steps reduced so far (device)
-    float* wall;          // full-way bounce-back: per-node fh of the previous step (state layout,
-                          // FP32 storage only), or nullptr for halfway bounce-back
+    bool fullway;         // full-way bounce-back (FP32 storage only): dst holds the state one step older than src
     bool pressure;        // Zou-He pressure faces at x = 0 and x = nx - 1 (FP32, bitmap, no field)
     float drho_in, drho_out;  // their density deviations rho - rho0
 };
