@@ -352,13 +352,13 @@ int lbm_set_pressure(lbm_ctx* ctx, int enable, double rho_in, double rho_out);
  * lbm_adjoint refuses a context with symmetry planes. */
 int lbm_set_symmetry(lbm_ctx* ctx, int mirror_y, int mirror_z);
 
-/* Host only.  With enable != 0 (the default), lbm_step and
- * lbm_run_to_steady run stretches of 32 steps, once a step is pending, by
- * replaying a HIP graph captured from the same launches on first use (one
- * launch call per 32 steps: small images are otherwise launch-bound).  The
- * results are identical to plain launches, which enable = 0 selects.  Any
- * change of collision, wall, pressure, force field or storage exponent drops
- * the captured graphs. */
+/* Host only.  With enable != 0 (the default), lbm_step,
+ * lbm_run_to_steady and lbm_adjoint run small images (up to 896 chunks of 256
+ * nodes) several steps a launch, and others in stretches of 32 steps, once a
+ * step is pending, by replaying a HIP graph captured from the same launches on
+ * first use.  The results are identical to one launch a step, which enable = 0
+ * selects.  Any change of collision, wall, pressure, force field or storage
+ * exponent drops the captured graphs. */
 int lbm_set_graphs(lbm_ctx* ctx, int enable);
 
 /* FP16 storage keeps 2^e (f_i - w_i rho0); e defaults to

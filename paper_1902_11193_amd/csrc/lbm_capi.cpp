@@ -7,8 +7,10 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "lbm_host.hpp"
@@ -56,7 +58,7 @@ size_t state_bytes(int storage, int64_t np) {
 
 // Workspace layout (byte offsets, each 256-aligned).
 struct Layout {
-    size_t A, B, table, coords, ent, wrap, count, partials, ring, total;
+    size_t A, B, table, coords, ent, wrap, count, sync, partials, ring, total;
 };
 
 Layout layout(int64_t np, int64_t nf, int storage, int index_kind, int nx, int ny, int nz) {
@@ -81,6 +83,8 @@ Layout layout(int64_t np, int64_t nf, int storage, int index_kind, int nx, int n
         L.count = off;
         off += align256((size_t)ny * nz * 16);
     }
+    L.sync = off;  // barrier memory of launch_steps
+    off += align256(lbm::kSyncBytes);
     // the reduction scratch, kReductionBytes at the end (lbm_setup_static
     // contexts keep it in the static array instead)
     L.partials = off;  // two buffers: steps alternate between them
@@ -152,6 +156,7 @@ struct lbm_ctx {
     lbm::IndexView idx;
     int grid;
     bool cached;  // the step's results stay in the caches (choose_launch)
+    int steps_fit;  // blocks of launch_steps that run at once with the current settings; -1: not asked yet
     double* partials[2];
     double* ring;
     uint32_t* ctr;      // steps reduced into the ring so far (device, after the ring)
@@ -165,6 +170,8 @@ struct lbm_ctx {
     bool graphs;
     hipStream_t cap_stream;
     hipGraphExec_t gexec[4];
+    int dev;           // the GPU of the workspace and stream
+    bool registered;   // counted in g_steps
     int static_dev;  // device whose static reduction scratch this context holds, or -1
     double adj_ms[3];  // last lbm_adjoint: forward, recompute and reverse milliseconds
     bool adj_timed;
@@ -180,11 +187,8 @@ lbm::RatesF rates_f(const lbm::RateClasses& r) {
 
 float scale_of(const lbm_ctx* c) { return std::ldexp(1.0f, c->exponent); }
 
-// One forward step from `src` to `dst` with partial sums into `partials`;
-// when prev_partials is non-null the same launch reduces them into the next
-// ring slot (the device counter's).
-hipError_t step_raw(lbm_ctx* c, const void* src, void* dst, double* partials, const double* prev_partials,
-                    hipStream_t stream, bool cached) {
+// What a step from `src` to `dst` with the context's settings launches.
+lbm::StepLaunch step_args(const lbm_ctx* c, const void* src, void* dst, double* partials) {
     lbm::StepLaunch a{};
     a.storage = c->storage;
     a.collision = c->collision;
@@ -203,16 +207,27 @@ hipError_t step_raw(lbm_ctx* c, const void* src, void* dst, double* partials, co
     a.field = c->field;
     a.scale = scale_of(c);
     a.inv_scale = 1.0f / a.scale;
-    a.cached = cached;
     a.grid = c->grid;
     a.partials = partials;
-    a.prev_partials = prev_partials;
     a.ring = c->ring;
     a.ctr = c->ctr;
+    return a;
+}
+
+// One forward step from `src` to `dst` with partial sums into `partials`;
+// when prev_partials is non-null the same launch reduces them into the next
+// ring slot (the device counter's).
+hipError_t step_raw(lbm_ctx* c, const void* src, void* dst, double* partials, const double* prev_partials,
+                    hipStream_t stream, bool cached) {
+    lbm::StepLaunch a = step_args(c, src, dst, partials);
+    a.cached = cached;
+    a.prev_partials = prev_partials;
     return lbm::launch_step(a, stream);
 }
 
+// After any change of what a step launch bakes in.
 void drop_graphs(lbm_ctx* c) {
+    c->steps_fit = -1;
     for (auto& g : c->gexec)
         if (g) {
             hipGraphExecDestroy(g);
@@ -257,7 +272,7 @@ hipGraphExec_t graph_for(lbm_ctx* c) {
 }
 
 // Bytes a step goes over: both states and the neighbour index.
-size_t index_bytes(const lbm_ctx* c) { return c->L.partials - std::max(c->L.table, c->L.coords); }
+size_t index_bytes(const lbm_ctx* c) { return c->L.sync - std::max(c->L.table, c->L.coords); }
 size_t step_bytes(const lbm_ctx* c) {
     return 2 * state_bytes(c->storage, c->np) + index_bytes(c);
 }
@@ -306,13 +321,144 @@ bool two_rate(const lbm::RateClasses& r) {
     return r.s_e == r.s_nu && r.s_eps == r.s_nu && r.s_pi == r.s_nu && r.s_m == r.s_q;
 }
 
+// Images of at most this many chunks take several steps a launch, one block
+// per chunk, where that many blocks run at once.  Beyond it the steps' traffic
+// past the XCDs' L2 costs more than the launches (us per step, 38% porous
+// packs, several / one a launch: 95 chunks 3.8 / 6.7, 261 4.8 / 8.1, 555 6.9 /
+// 10.2, 760 9.1 / 10.5, 1012 13.2 / 12.6; FP16 760 7.7 / 10.3; F16R 760 9.6 /
+// 13.0; full-way walls and mirror planes 760 9.8 / 11.5).
+constexpr int64_t kStepsChunks = 896;
+static_assert(kStepsChunks <= lbm::kStepsBlocks, "the barrier memory has a word per block");
+constexpr int kStepsLeast = 4;      // steps worth such a launch
+constexpr int kStepsMost = 512;     // steps a launch takes at most
+// The block sums of all steps of a launch share the two partial buffers.
+int steps_per_launch(const lbm_ctx* c) {
+    const int64_t chunks = c->np / lbm::kChunk;
+    return (int)std::min<int64_t>(kStepsMost, (int64_t)(2 * lbm::kPartialBytes / (4 * sizeof(double))) / chunks);
+}
+bool several_steps(lbm_ctx* c) {
+    const int64_t chunks = c->np / lbm::kChunk;
+    if (!c->graphs || chunks > kStepsChunks) return false;
+    // a captured launch may be replayed beside any other
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    if (c->steps_fit < 0) {
+        int per_cu = 0;
+        const hipError_t he = lbm::steps_occupancy(step_args(c, c->cur, c->nxt, c->partials[0]), &per_cu);
+        c->steps_fit = he == hipSuccess ? per_cu * std::max(c->cus, 1) : 0;
+    }
+    return chunks <= c->steps_fit;
+}
+
 // Step n (0-based) writes partials[n % 2]; its launch also reduces the
 // partials of step n-1 into the ring.  With a step pending, runs of
 // kGraphSteps steps replay a captured graph (one launch call instead of
 // kGraphSteps; the launches and their arguments are the same).
+int flush(lbm_ctx* c);
+
+// Launches of several steps need all their blocks running at once, so those of
+// different streams must fit the GPU together.  For every stream that a live
+// context works on: the share of the GPU its last such launch takes, and an
+// event recorded behind it.  With one stream (the usual case) nothing is
+// recorded, as its launches follow each other.  With more, a launch that does
+// not fit beside those still in flight waits, on the GPU, for the oldest of
+// them.  The kernel
+// itself stays correct where it does not get its room (k_steps).
+struct StepsInFlight {
+    int contexts = 0;
+    hipEvent_t event = nullptr;
+    double share = 0.0;
+    uint64_t launch = 0, waited = 0;   // its number, and that of the last launch that waits for it
+};
+std::mutex g_steps_mu;
+uint64_t g_launch = 1;
+std::map<std::pair<int, hipStream_t>, StepsInFlight> g_steps;   // by device and stream
+
+// A second stream on the GPU: what the first has in flight was not recorded.
+void record_first(int dev) {
+    StepsInFlight* first = nullptr;
+    hipStream_t stream = nullptr;
+    for (auto& [key, s] : g_steps)
+        if (key.first == dev) {
+            if (first) return;  // more than one already
+            first = &s;
+            stream = key.second;
+        }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!first || hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+    if (!first->event && hipEventCreateWithFlags(&first->event, hipEventDisableTiming) != hipSuccess) {
+        first->event = nullptr;
+        return;
+    }
+    if (hipEventRecord(first->event, stream) == hipSuccess) first->share = 1.0;
+}
+void steps_register(lbm_ctx* c) {
+    std::lock_guard<std::mutex> lock(g_steps_mu);
+    if (!g_steps.count({c->dev, c->stream})) record_first(c->dev);
+    ++g_steps[{c->dev, c->stream}].contexts;
+    c->registered = true;
+}
+void steps_unregister(lbm_ctx* c) {
+    if (!c->registered) return;
+    std::lock_guard<std::mutex> lock(g_steps_mu);
+    const auto it = g_steps.find({c->dev, c->stream});
+    if (it == g_steps.end() || --it->second.contexts > 0) return;
+    if (it->second.event) hipEventDestroy(it->second.event);
+    g_steps.erase(it);
+}
+
+hipError_t run_steps(lbm_ctx* c, const lbm::StepLaunch& a, int steps, void* second, int64_t stride) {
+    uint32_t* sync = reinterpret_cast<uint32_t*>(c->ws + c->L.sync);
+    std::lock_guard<std::mutex> lock(g_steps_mu);
+    size_t streams = 0;
+    for (const auto& s : g_steps) streams += s.first.first == c->dev;
+    if (streams < 2) return lbm::launch_steps(a, steps, second, stride, sync, c->stream);
+    StepsInFlight& mine = g_steps[{c->dev, c->stream}];
+    const double share = (double)(c->np / lbm::kChunk) / std::max(c->steps_fit, 1);
+    double others = 0.0;
+    for (auto& [key, s] : g_steps) {
+        if (key.first != c->dev || s.share == 0.0) continue;
+        if (hipEventQuery(s.event) == hipSuccess)
+            s.share = 0.0;
+        else
+            (void)hipGetLastError();  // not ready
+        if (&s != &mine) others += s.share;
+    }
+    hipError_t he = hipSuccess;
+    while (he == hipSuccess && others + share > 1.0) {  // behind the oldest, until the rest leaves room
+        StepsInFlight* oldest = nullptr;
+        for (auto& [key, s] : g_steps)
+            if (key.first == c->dev && &s != &mine && s.share > 0.0 && s.waited != g_launch &&
+                (!oldest || s.launch < oldest->launch))
+                oldest = &s;
+        if (!oldest) break;
+        he = hipStreamWaitEvent(c->stream, oldest->event, 0);
+        oldest->waited = g_launch;
+        others -= oldest->share;
+    }
+    if (he == hipSuccess && !mine.event) he = hipEventCreateWithFlags(&mine.event, hipEventDisableTiming);
+    if (he == hipSuccess) he = lbm::launch_steps(a, steps, second, stride, sync, c->stream);
+    if (he == hipSuccess) he = hipEventRecord(mine.event, c->stream);
+    if (he == hipSuccess) {
+        mine.share = std::max(mine.share, share);
+        mine.launch = g_launch++;
+    }
+    return he;
+}
+
 int do_steps(lbm_ctx* c, int n) {
     int k = 0;
     while (k < n) {
+        if (n - k >= kStepsLeast && several_steps(c)) {
+            int rc = flush(c);
+            if (rc) return rc;
+            const int m = std::min(n - k, steps_per_launch(c));
+            HIP_TRY(run_steps(c, step_args(c, c->cur, c->nxt, c->partials[0]), m, c->cur, 0));
+            if (m & 1) std::swap(c->cur, c->nxt);
+            c->steps += m;
+            k += m;
+            continue;
+        }
         if (c->graphs && c->pending && n - k >= kGraphSteps) {
             hipGraphExec_t g = graph_for(c);
             if (g) {
@@ -475,6 +621,7 @@ const lbm_ctx* g_static_owner[kStaticDevices] = {};
 }  // namespace
 
 lbm_ctx::~lbm_ctx() {
+    steps_unregister(this);
     for (auto& g : gexec)
         if (g) hipGraphExecDestroy(g);
     if (cap_stream) hipStreamDestroy(cap_stream);
@@ -555,6 +702,7 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
     c->ring = reinterpret_cast<double*>(rbase + (c->L.ring - c->L.partials));
     c->ctr = reinterpret_cast<uint32_t*>(c->ring + (size_t)kRing * 4);
     c->graphs = true;
+    c->steps_fit = -1;
     c->cap_stream = nullptr;
     for (auto& g : c->gexec) g = nullptr;
     c->steps = 0;
@@ -592,6 +740,7 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
     hipError_t he = hipGetDevice(&dev);
     if (he == hipSuccess) he = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (he != hipSuccess) return cleanup(fail(LBM_EHIP, std::string("device query: ") + hipGetErrorString(he)));
+    c->dev = dev;
     he = choose_launch(c);
     if (he != hipSuccess) return cleanup(fail(LBM_EHIP, std::string("occupancy query: ") + hipGetErrorString(he)));
 
@@ -634,9 +783,11 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
                                 c->stream);
     }
     if (he == hipSuccess) he = lbm::launch_zero(c->ws + c->L.A, (int64_t)(c->L.B - c->L.A) * 2, c->stream);
+    if (he == hipSuccess) he = lbm::launch_zero(c->ws + c->L.sync, (int64_t)lbm::kSyncBytes, c->stream);
     if (he == hipSuccess) he = zero_ring(c);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
     if (he != hipSuccess) return cleanup(fail(LBM_EHIP, std::string("setup upload: ") + hipGetErrorString(he)));
+    steps_register(c);
     *ctx = c;
     return LBM_OK;
 }
@@ -1110,12 +1261,14 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     HIP_TRY(zero_ring(c));
     c->steps = 0;
     c->pending = false;
-    for (int n = 0; n < N; ++n) {
-        if (n % K == 0 && n / K < A.nsnap && n <= N - 1)
+    for (int n = 0; n < N;) {
+        if (n % K == 0 && n / K < A.nsnap)
             HIP_TRY(hipMemcpyAsync(snap(n / K), c->cur, (size_t)19 * c->np * 4,
                                    hipMemcpyDeviceToDevice, c->stream));
-        int rc = do_steps(c, 1);
+        const int run = std::min(K - n % K, N - n);  // to the next snapshot
+        int rc = do_steps(c, run);
         if (rc) return rc;
+        n += run;
     }
     HIP_TRY(timer.mark(kPhaseOther, c->stream));
     double u[3];
@@ -1152,9 +1305,16 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
         const int n1 = std::min((s + 1) * K, nrev);  // last reverse step of the segment
         // recompute fh^{n0+1} .. fh^{n1-1}
         HIP_TRY(timer.mark(kPhaseRecompute, c->stream));
-        for (int t = 1; t < n1 - n0; ++t) {
+        for (int t = 1; t < n1 - n0;) {
             const void* src = t == 1 ? (const void*)snap(s) : (const void*)seg(t - 1);
-            HIP_TRY(step_raw(c, src, seg(t), scratch4, nullptr, c->stream, al.cached));
+            const int run = std::min(n1 - n0 - t, kStepsMost);
+            if (run >= kStepsLeast && several_steps(c)) {
+                HIP_TRY(run_steps(c, step_args(c, src, seg(t), nullptr), run, nullptr, (int64_t)state));
+                t += run;
+            } else {
+                HIP_TRY(step_raw(c, src, seg(t), scratch4, nullptr, c->stream, al.cached));
+                ++t;
+            }
         }
         HIP_TRY(timer.mark(kPhaseReverse, c->stream));
         for (int n = n1; n > n0; --n) {

@@ -107,6 +107,11 @@ struct CodecF16R {
     using T = _Float16;
     static constexpr int kSlots = 19;
     static constexpr bool kRef = true;
+    // inv is a power of two: only the product with the weight rounds.  The form
+    // is written out so that every kernel rounds alike.
+    static __device__ __forceinline__ float cvt_ref(T v, float inv, float w, T ref) {
+        return __builtin_fmaf((float)v, inv, w * (float)ref);
+    }
     static __device__ __forceinline__ float cvt(T v, float inv) { return (float)v * inv; }
     static __device__ __forceinline__ T enc(float v, float s) { return (_Float16)(v * s); }
 };
@@ -123,6 +128,40 @@ template <class T>
 __device__ __forceinline__ void st_off(T* base, uint32_t byte_off, T v) {
     *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off) = v;
 }
+// How a kernel reads and writes the states.  Plain: through the caches.
+// Shared: where blocks on different XCDs exchange values inside one launch
+// (k_steps), each access goes to the level they share (agent scope), past the
+// XCD's own L2.
+struct Plain {
+    template <class T>
+    static __device__ __forceinline__ T ld(const T* base, uint32_t byte_off) {
+        return ld_off(base, byte_off);
+    }
+    static __device__ __forceinline__ void ld2(const uint32_t* base, uint32_t byte_off, uint32_t v[2]) {
+        typedef uint32_t U2 __attribute__((ext_vector_type(2), aligned(4)));
+        const U2 t = ld_off(reinterpret_cast<const U2*>(base), byte_off);
+        v[0] = t.x;
+        v[1] = t.y;
+    }
+};
+struct Shared {
+    template <class T>
+    static __device__ __forceinline__ T ld(const T* base, uint32_t byte_off) {
+        using U = std::conditional_t<sizeof(T) == 4, uint32_t, uint16_t>;
+        const U* p = reinterpret_cast<const U*>(reinterpret_cast<const char*>(base) + byte_off);
+        return __builtin_bit_cast(T, __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
+    static __device__ __forceinline__ void ld2(const uint32_t* base, uint32_t byte_off, uint32_t v[2]) {
+        v[0] = ld(base, byte_off);
+        v[1] = ld(base + 1, byte_off);
+    }
+    template <class T>
+    static __device__ __forceinline__ void st(T* base, uint32_t byte_off, T v) {
+        using U = std::conditional_t<sizeof(T) == 4, uint32_t, uint16_t>;
+        U* p = reinterpret_cast<U*>(reinterpret_cast<char*>(base) + byte_off);
+        __hip_atomic_store(p, __builtin_bit_cast(U, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
 // Streaming store, for states larger than the caches: the next step reads
 // these values only after the whole population array (gigabytes) has gone
 // through the caches, so they are written without displacing cached lines
@@ -268,12 +307,12 @@ struct TableIdx {
     struct RefLoads {
         T v[19];
     };
-    template <class T, int S>
+    template <class M, class T, int S>
     __device__ __forceinline__ void issue_refs(const RefPlan& plan, const T* rb, uint32_t, const uint32_t*,
                                                uint32_t, uint32_t, RefLoads<T>& L) const {
         unroll<19>([&](auto k) {
             constexpr int i = decltype(k)::value;
-            L.v[i] = ld_off(rb, plan.ro[i]);
+            L.v[i] = M::ld(rb, plan.ro[i]);
         });
     }
     template <class T>
@@ -594,14 +633,14 @@ struct BitmapIdx {
         uint64_t win[9];
         T wrap[5];  // across the x wrap: sources of c_x = +1 (x = 0) or c_x = -1 (x = nx - 1)
     };
-    template <class T, int S>
+    template <class M, class T, int S>
     __device__ __forceinline__ void issue_refs(const RefPlan& plan, const T* rb, uint32_t wb, const uint32_t* off,
                                                uint32_t chunk, uint32_t slack, RefLoads<T>& L) const {
-        typedef uint32_t U2 __attribute__((ext_vector_type(2), aligned(4)));
         unroll<9>([&](auto k) {
             constexpr int R = decltype(k)::value;
-            const U2 v = ld_off(reinterpret_cast<const U2*>(rb), plan.ro[R]);
-            L.win[R] = (uint64_t)v.x | ((uint64_t)v.y << 32);
+            uint32_t v[2];
+            M::ld2(reinterpret_cast<const uint32_t*>(rb), plan.ro[R], v);
+            L.win[R] = (uint64_t)v[0] | ((uint64_t)v[1] << 32);
         });
         if (plan.xw) {
             // Node m of a pulled value i from its offset: the load reads element
@@ -617,7 +656,7 @@ struct BitmapIdx {
                     const uint64_t ne = (uint64_t)chunk * (S * kThreads) - slack + o / (uint32_t)sizeof(T) -
                                         (uint64_t)i * kThreads;
                     const uint32_t m = (uint32_t)(ne / (S * kThreads)) * kThreads + (uint32_t)(ne % (S * kThreads));
-                    L.wrap[decltype(k)::value] = ld_off(rb, m * (uint32_t)sizeof(T));
+                    L.wrap[decltype(k)::value] = M::ld(rb, m * (uint32_t)sizeof(T));
                 }
             });
         }
@@ -853,7 +892,9 @@ __device__ __forceinline__ TrtOut collide_trt(float f[19], float Fx, float Fy, f
 }
 
 // ------------------------------------------------------------------ reductions
-template <int K>
+// SHARED: the sums go to the level all XCDs share, for another block of the
+// same launch to read.
+template <int K, bool SHARED = false>
 __device__ __forceinline__ void block_sum(double (&v)[K], double* out) {
     __shared__ double red[kThreads / 64][K];
 #pragma unroll
@@ -868,7 +909,10 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double* out) {
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < kThreads / 64; ++w) s += red[w][threadIdx.x];
-        out[threadIdx.x] = s;
+        if constexpr (SHARED)
+            __hip_atomic_store(out + threadIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            out[threadIdx.x] = s;
     }
 }
 
@@ -934,6 +978,35 @@ k_finalize_ring(const double* __restrict__ partials, int grid, double* __restric
 }
 
 // ------------------------------------------------------------------ step
+// Pressure faces and collision of node n: its gathered deviations f in, the
+// post-collision ones out.  Returns the shifted momentum and the density
+// deviation for the reduction.
+struct Moved {
+    float jx, jy, jz, drho;
+};
+template <bool FIELD, bool TRT, bool ZH>
+__device__ __forceinline__ Moved collide_node(float f[19], uint32_t n, uint32_t nf, uint32_t side, const RatesF& r,
+                                              float Fx, float Fy, float Fz, const float* __restrict__ field,
+                                              float drho_in, float drho_out) {
+    if constexpr (ZH) {
+        if (side != 0u) zou_he(f, side, drho_in, drho_out);
+    }
+    if (FIELD) {
+        Fx = field[n];
+        Fy = field[nf + n];
+        Fz = field[2 * nf + n];
+    }
+    if constexpr (TRT) {
+        const TrtOut o = collide_trt(f, Fx, Fy, Fz, r.s_nu, r.s_q);
+        return Moved{o.jx, o.jy, o.jz, o.rho};
+    } else {
+        const Mom m = moments(f);
+        const float jx = m.jx + 0.5f * Fx, jy = m.jy + 0.5f * Fy, jz = m.jz + 0.5f * Fz;
+        add_back(f, collide_increment(m, jx, jy, jz, Fx, Fy, Fz, r));
+        return Moved{jx, jy, jz, m.rho};
+    }
+}
+
 // FW: full-way bounce-back (Sec. 2.3).  A population sent into a wall comes
 // back one step later than with the halfway wall, so at a wall link the node
 // takes its own fh_opp(i) of two steps ago.  The states ping-pong, so that is
@@ -1016,7 +1089,7 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
             // REF: the reference density of the node each value came from: the
             // source node, or the node itself at a wall
             typename Ix::template RefLoads<T> refl;
-            if constexpr (REF) ix.template issue_refs<T, S>(plan, rsrc, wb, off, c, slack, refl);
+            if constexpr (REF) ix.template issue_refs<Plain, T, S>(plan, rsrc, wb, off, c, slack, refl);
             const typename Ix::RefPlan plan_n = plan;
             // a lane's own slot in chunk c: node c * 256 + lane, or for a lane
             // past the list a padded slot that no other lane reads or writes
@@ -1042,8 +1115,10 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
             float f[19];
             unroll<19>([&](auto k) {
                 constexpr int i = decltype(k)::value;
-                f[i] = C::cvt(fr[i], inv);
-                if constexpr (REF) f[i] += wgt(i) * (float)rr[i];
+                if constexpr (REF)
+                    f[i] = C::cvt_ref(fr[i], inv, wgt(i), rr[i]);
+                else
+                    f[i] = C::cvt(fr[i], inv);
             });
             if constexpr (FW) {
                 // wall link i: the value of two steps ago
@@ -1053,44 +1128,21 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
                     f[i] = __uint_as_float(bit_select(w, __float_as_uint(wv[i]), __float_as_uint(f[i])));
                 });
             }
-            if constexpr (ZH) {
-                if (side_n != 0u) zou_he(f, side_n, drho_in, drho_out);
-            }
-            float Fx = Fx0, Fy = Fy0, Fz = Fz0;
-            if (FIELD) {
-                Fx = field[n];
-                Fy = field[nf + n];
-                Fz = field[2 * nf + n];
-            }
-            float jx, jy, jz, drho;
-            if constexpr (TRT) {
-                const TrtOut o = collide_trt(f, Fx, Fy, Fz, r.s_nu, r.s_q);
-                jx = o.jx;
-                jy = o.jy;
-                jz = o.jz;
-                drho = o.rho;
-            } else {
-                const Mom m = moments(f);
-                jx = m.jx + 0.5f * Fx;
-                jy = m.jy + 0.5f * Fy;
-                jz = m.jz + 0.5f * Fz;
-                drho = m.rho;
-                add_back(f, collide_increment(m, jx, jy, jz, Fx, Fy, Fz, r));
-            }
+            const Moved mv = collide_node<FIELD, TRT, ZH>(f, n, nf, side_n, r, Fx0, Fy0, Fz0, field, drho_in, drho_out);
             // Lanes past the list carry n = nf - 1 for their loads and write
             // their results to their own padded slots (element lane of the
             // last chunk), which nothing reads, so the stores stay
             // unconditional (no branch for the compiler to sink the gathers
             // into); the reduction leaves them out.
             const bool live = c * kThreads + threadIdx.x < nf;
-            acc[0] += live ? (double)jx : 0.0;
-            acc[1] += live ? (double)jy : 0.0;
-            acc[2] += live ? (double)jz : 0.0;
-            acc[3] += live ? (double)drho : 0.0;
+            acc[0] += live ? (double)mv.jx : 0.0;
+            acc[1] += live ? (double)mv.jy : 0.0;
+            acc[2] += live ? (double)mv.jz : 0.0;
+            acc[3] += live ? (double)mv.drho : 0.0;
             if constexpr (REF) {
                 // the node's new reference: its density deviation, which the
                 // collision conserves, rounded to the stored type
-                const T r_new = (T)drho;
+                const T r_new = (T)mv.drho;
                 const float rf = (float)r_new;
                 st_state<CACHED>(rdst + (size_t)c * kThreads, so, r_new);
                 unroll<19>([&](auto k) {
@@ -1111,6 +1163,290 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
         }
     }
     block_sum<4>(acc, partials + (size_t)lb * 4);
+}
+
+// ------------------------------------------------------------------ several steps in one launch
+// For images of few chunks a step launched by itself is a chain of latencies:
+// launch, packed coordinate, index entries, gathers, the block sums, and in
+// block 0 the reduction of the step before (6 to 7 us whatever the size).
+// Here each block keeps one chunk for `steps` steps: the gather offsets stay
+// in registers, and a block counts the steps it has finished in a word of its
+// own, once its stores have been acknowledged.  Before it goes on it waits for
+// the blocks it gathers from alone (links have two ends, so those are also the
+// blocks that read what it overwrites next): polling every block's word made
+// the polls of all blocks meet in the same few cache lines (120 blocks 6.0 us a
+// step, 202 blocks 6.8; waiting for neighbours 4.1 and 4.0).
+// What blocks exchange goes past their XCD's L2 (Shared), so no cache is
+// flushed or invalidated.  The block sums of all steps are kept and reduced
+// after the last one, in the order the single-step launches use (the same
+// results bit for bit).  Measured, one launch a step -> here, us per step: the
+// 13 chunks of a bore 32 voxels wide 6.0 -> 3.3, the 32^3 sphere array, 120
+// chunks, 6.7 -> 3.8, the 202 chunks of a bore 128 voxels wide 6.6 -> 3.7.  What
+// is left is the way of a value between blocks: store, its acknowledgement,
+// the word, the poll that sees it, the gather, and 0.5 us of arithmetic.
+//
+// The waits need every block to be running at once, which a launch does
+// not promise (other kernels may hold the GPU, other launches like this one
+// wait for room too).  So the blocks first count themselves in (sync[0]).  If
+// one has waited kMeetTicks (sync[2] where that is set) and they are not all
+// there, it closes the count
+// and takes all steps of all chunks by itself; every other block then leaves.
+// The count decides once, atomically, so either all blocks run together or
+// one runs alone, and no block waits for one that may not come.
+//
+// State t of the launch is read from `first` (t = 0) or written by step t - 1
+// to out + ((t - 1) % 2) * stride (ping-pong) or out + (t - 1) * stride.
+struct StepsArgs {
+    const void* first;    // state before the first step
+    void* out[2];         // where steps 0, 2, ... and 1, 3, ... write (PING), else out[0] + t * stride
+    int64_t stride;       // bytes between successive states; 0: ping-pong between out[0] and out[1]
+    const float* field;
+    double* partials;     // [steps][gridDim.x][4], or nullptr: no sums wanted
+    double* ring;
+    uint32_t* ctr;
+    uint32_t* sync;       // kSyncBytes, zero before the first launch
+    uint32_t slack, nf, steps;
+    RatesF r;
+    float F[3], scale, inv, drho_in, drho_out;
+};
+constexpr uint32_t kClosed = 0x80000000u;   // sync[0]: the count is closed, one block runs alone
+constexpr int64_t kMeetTicks = 10000000;    // 0.1 s of the 100 MHz clock
+constexpr int64_t kStuckTicks = 2000000000; // 20 s: no block came (a lost GPU); sums become NaN
+
+__device__ __forceinline__ uint32_t ld_sync(const uint32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Thread 0 of a block counts it in.  0: all blocks are here; 1: this block
+// runs alone; 2: another one does, leave.
+__device__ __forceinline__ int count_in(uint32_t* sync, uint32_t blocks) {
+    uint32_t v = __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    const uint32_t set = ld_sync(sync + 2);
+    const int64_t most = set ? (int64_t)set : kMeetTicks, t0 = wall_clock64();
+    while (!(v & kClosed) && v < blocks) {
+        if (wall_clock64() - t0 > most) {
+            if (__hip_atomic_compare_exchange_strong(sync, &v, v | kClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                return 1;
+            continue;  // v holds the count as it is now
+        }
+        v = ld_sync(sync);
+    }
+    return (v & kClosed) ? 2 : 0;
+}
+// One block leaves a closed count; the last of them resets it.
+__device__ __forceinline__ void count_out(uint32_t* sync, uint32_t blocks) {
+    if (__hip_atomic_fetch_add(sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == blocks) {
+        __hip_atomic_store(sync + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(sync, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
+__global__ void __launch_bounds__(kThreads)
+k_steps(const StepsArgs a, Ix ix) {
+    using T = typename C::T;
+    constexpr int S = C::kSlots;
+    constexpr bool REF = C::kRef;
+    __shared__ int s_word;
+    __shared__ uint32_t s_mask[kStepsBlocks / 32], s_count;
+    __shared__ uint16_t s_near[kStepsBlocks];   // the blocks this one gathers from
+    const uint32_t G = gridDim.x;   // = chunks
+    // steps finished by block b, over all launches
+    auto done = [&](uint32_t b) { return a.sync + kSyncHead + b * kSyncStride; };
+    if (threadIdx.x == 0) s_word = count_in(a.sync, G);
+    __syncthreads();
+    const int mode = s_word;
+    __syncthreads();
+    if (mode == 2) {
+        if (threadIdx.x == 0) count_out(a.sync, G);
+        return;
+    }
+    const bool alone = mode == 1;
+    // The other blocks of a closed count change nothing but sync[0] and
+    // sync[1], so `done` and `ctr` stand still until the launch's own writes.
+    const uint32_t before = ld_sync(done(blockIdx.x));
+    const uint32_t slot0 = ld_sync(a.ctr);
+
+    uint32_t c = alone ? 0u : blockIdx.x;
+    uint32_t n, off[19], wb = 0, side = 0;
+    typename Ix::RefPlan plan;
+    auto place = [&] {  // the gathers of chunk c
+        n = min(c * kThreads + threadIdx.x, a.nf - 1);
+        const typename Ix::Pre p = ix.prefetch(n);
+        typename Ix::Raw raw;
+        ix.load(n, p, raw);
+        if constexpr (REF)
+            ix.template offsets_ref<T, S>(raw, p, n, c, a.slack, off, wb, plan);
+        else
+            ix.template offsets<T, S, FW, SYM>(raw, p, n, c, a.slack, off, wb);
+        if constexpr (ZH) side = ix.x_face(p);
+    };
+    place();
+    if (!alone) {
+        if (threadIdx.x < kStepsBlocks / 32) s_mask[threadIdx.x] = 0u;
+        if (threadIdx.x == 0) s_count = 0u;
+        __syncthreads();
+        unroll<18>([&](auto k) {  // the chunk each value is gathered from
+            const uint32_t q =
+                (off[decltype(k)::value + 1] / (uint32_t)sizeof(T) - a.slack + c * kChunkElems) / kChunkElems;
+            if (q != c) atomicOr(&s_mask[q / 32u], 1u << (q % 32u));
+        });
+        __syncthreads();
+        for (uint32_t b = threadIdx.x; b < G; b += kThreads)
+            if ((s_mask[b / 32u] >> (b % 32u)) & 1u) s_near[atomicAdd(&s_count, 1u)] = (uint16_t)b;
+        __syncthreads();
+    }
+    const uint32_t so = threadIdx.x * (uint32_t)sizeof(T);
+    auto step = [&](uint32_t t) {  // step t of chunk c
+        auto state = [&](uint32_t k) -> T* {  // written by step k
+            return static_cast<T*>(a.stride ? static_cast<void*>(static_cast<char*>(a.out[0]) + (int64_t)k * a.stride)
+                                            : a.out[k & 1u]);
+        };
+        const T* src = t == 0 ? static_cast<const T*>(a.first) : state(t - 1);
+        T* dst = state(t);
+        const T* gb = chunk_base<T, S>(src, c, a.slack);
+        T* db = dst + (size_t)c * (S * kThreads);
+        T fr[19];
+        unroll<19>([&](auto k) {
+            constexpr int i = decltype(k)::value;
+            fr[i] = Shared::ld(gb, off[i]);
+        });
+        typename Ix::template RefLoads<T> refl;
+        if constexpr (REF)
+            ix.template issue_refs<Shared, T, S>(plan, src + (size_t)G * (S * kThreads), wb, off, c, a.slack, refl);
+        T wv[19];
+        if constexpr (FW)
+            unroll<18>([&](auto k) {
+                constexpr int i = decltype(k)::value + 1;
+                wv[i] = Shared::ld(db + opp(i) * kThreads, so);
+            });
+        T rr[19];
+        if constexpr (REF) ix.finish_refs(plan, wb, refl, rr);
+        float f[19];
+        unroll<19>([&](auto k) {
+            constexpr int i = decltype(k)::value;
+            if constexpr (REF)
+                f[i] = C::cvt_ref(fr[i], a.inv, wgt(i), rr[i]);
+            else
+                f[i] = C::cvt(fr[i], a.inv);
+        });
+        if constexpr (FW)
+            unroll<18>([&](auto k) {
+                constexpr int i = decltype(k)::value + 1;
+                const uint32_t w = (uint32_t)__builtin_amdgcn_sbfe((int32_t)wb, (uint32_t)i, 1u);
+                f[i] = __uint_as_float(
+                    bit_select(w, __float_as_uint(C::cvt(wv[i], a.inv)), __float_as_uint(f[i])));
+            });
+        const Moved mv = collide_node<FIELD, TRT, ZH>(f, n, a.nf, side, a.r, a.F[0], a.F[1], a.F[2], a.field,
+                                                      a.drho_in, a.drho_out);
+        if constexpr (REF) {
+            const T r_new = (T)mv.drho;
+            const float rf = (float)r_new;
+            Shared::st(dst + (size_t)G * (S * kThreads) + (size_t)c * kThreads, so, r_new);
+            unroll<19>([&](auto k) {
+                constexpr int i = decltype(k)::value;
+                Shared::st(db + i * kThreads, so, C::enc(f[i] - wgt(i) * rf, a.scale));
+            });
+        } else {
+            unroll<19>([&](auto k) {
+                constexpr int i = decltype(k)::value;
+                Shared::st(db + i * kThreads, so, C::enc(f[i], a.scale));
+            });
+        }
+        // every wave's stores are acknowledged before the block goes on
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        return mv;
+    };
+    auto sum = [&](uint32_t t, const Moved& mv) {  // the block sums of step t
+        if (!a.partials) return;
+        const bool live = c * kThreads + threadIdx.x < a.nf;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        acc[0] += live ? (double)mv.jx : 0.0;
+        acc[1] += live ? (double)mv.jy : 0.0;
+        acc[2] += live ? (double)mv.jz : 0.0;
+        acc[3] += live ? (double)mv.drho : 0.0;
+        block_sum<4, true>(acc, a.partials + ((size_t)t * G + c) * 4);
+    };
+    // this block has finished `count` steps
+    auto tell = [&](uint32_t count) {
+        if (threadIdx.x == 0) __hip_atomic_store(done(blockIdx.x), count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // one wave waits until the blocks which(0 .. count - 1) have finished `target` steps
+    auto wait = [&](uint32_t count, auto which, uint32_t target) {
+        if (threadIdx.x < 64) {
+            int64_t t0 = 0;
+            uint32_t polls = 0;
+            for (uint32_t k = threadIdx.x; k < count; k += 64)
+                while ((int32_t)(ld_sync(done(which(k))) - target) < 0) {
+                    if (++polls % 1024u != 0) continue;
+                    if (t0 == 0) t0 = wall_clock64();
+                    if (wall_clock64() - t0 > kStuckTicks) {
+                        s_word = -1;
+                        break;
+                    }
+                }
+        }
+        __syncthreads();
+        return s_word != -1;
+    };
+    bool stuck = false;
+    for (uint32_t t = 0; t < a.steps && !stuck; ++t) {
+        if (alone) {
+            for (c = 0; c < G; ++c) {
+                place();
+                sum(t, step(t));
+                __syncthreads();
+            }
+            continue;
+        }
+        const Moved mv = step(t);
+        tell(before + t + 1u);
+        sum(t, mv);   // while the word travels
+        if (t + 1u < a.steps) {
+            stuck = !wait(s_count, [&](uint32_t k) { return (uint32_t)s_near[k]; }, before + t + 1u);
+        } else {      // all blocks, their sums written
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            tell(before + t + 2u);
+            stuck = !wait(G, [&](uint32_t k) { return k; }, before + t + 2u);
+        }
+    }
+    if (alone) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    // All steps are done and their sums written: reduce them, step s by block
+    // s % G (by this one when it runs alone), or for few blocks by one wave
+    // each, which adds in the order reduce_partials does.
+    if (a.partials) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const uint32_t share = G <= 64 ? kThreads / 64 : 1;   // steps a block reduces at a time
+        const uint32_t s0 = (alone ? 0u : blockIdx.x) * share, ds = (alone ? 1u : G) * share;
+        const uint32_t wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+        for (uint32_t q = s0; q < a.steps; q += ds) {
+            const uint32_t s = share > 1 ? q + wave : q;
+            double* out = a.ring + (size_t)((slot0 + s) % kRingSlots) * 4;
+            if (share > 1) {
+                if (s >= a.steps) continue;
+                double v[4];
+                for (int k = 0; k < 4; ++k) {
+                    v[k] = lane < G ? 0.0 + a.partials[((size_t)s * G + lane) * 4 + k] : 0.0;
+                    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+                    if (lane == 0) out[k] = stuck ? __builtin_nan("") : 0.0 + v[k];
+                }
+            } else if (stuck) {
+                if (threadIdx.x < 4) out[threadIdx.x] = __builtin_nan("");
+            } else {
+                reduce_partials<4>(a.partials + (size_t)s * G * 4, (int)G, out);
+                __syncthreads();
+            }
+        }
+    }
+    if (threadIdx.x == 0 && (alone || blockIdx.x == 0)) {
+        if (a.partials) *a.ctr = slot0 + a.steps;
+        if (!alone) __hip_atomic_store(a.sync, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (alone && threadIdx.x == 0) count_out(a.sync, G);
 }
 
 __global__ void k_zero(uint32_t* p, int64_t words) {
@@ -1368,70 +1704,116 @@ BitmapIdx bitmap_view(const IndexView& v) {
                      mz ? 0u : wrap, mz ? 0u : 0u - wrap, (uint32_t)v.sym};
 }
 
-template <class C, class Ix, bool CACHED, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
-hipError_t step_kernel(const StepLaunch& a, Ix ix, hipStream_t s) {
-    using T = typename C::T;
-    hipLaunchKernelGGL((k_step<C, Ix, CACHED, FIELD, TRT, FW, ZH, SYM>), dim3(a.grid), dim3(kThreads), 0, s,
-                       static_cast<const T*>(a.src), static_cast<T*>(a.dst), ix, (uint32_t)a.idx.slack,
-                       (uint32_t)a.nf, a.rates, a.F[0], a.F[1], a.F[2], FIELD ? a.field : nullptr, a.scale,
-                       a.inv_scale, a.partials, a.prev_partials, a.ring, a.ctr,
-                       ZH ? a.drho_in : 0.f, ZH ? a.drho_out : 0.f);
-    return hipGetLastError();
-}
-template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
-hipError_t step_stores(const StepLaunch& a, Ix ix, hipStream_t s) {
-    if (a.cached) return step_kernel<C, Ix, true, FIELD, TRT, FW, ZH, SYM>(a, ix, s);
-    return step_kernel<C, Ix, false, FIELD, TRT, FW, ZH, SYM>(a, ix, s);
-}
-template <class C, class Ix, bool TRT, bool FW, bool SYM = false>
-hipError_t step_launch(const StepLaunch& a, Ix ix, hipStream_t s) {
-    if (a.field) return step_stores<C, Ix, true, TRT, FW, false, SYM>(a, ix, s);
-    return step_stores<C, Ix, false, TRT, FW, false, SYM>(a, ix, s);
-}
+// What to do with the step kernel of a launch: run one step, run several in
+// one launch (k_steps), or ask how many blocks of k_steps fit a compute unit.
+struct RunStep {
+    template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
+    hipError_t run(const StepLaunch& a, Ix ix, hipStream_t s) const {
+        if (a.cached) return one<C, Ix, true, FIELD, TRT, FW, ZH, SYM>(a, ix, s);
+        return one<C, Ix, false, FIELD, TRT, FW, ZH, SYM>(a, ix, s);
+    }
+    template <class C, class Ix, bool CACHED, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
+    static hipError_t one(const StepLaunch& a, Ix ix, hipStream_t s) {
+        using T = typename C::T;
+        hipLaunchKernelGGL((k_step<C, Ix, CACHED, FIELD, TRT, FW, ZH, SYM>), dim3(a.grid), dim3(kThreads), 0, s,
+                           static_cast<const T*>(a.src), static_cast<T*>(a.dst), ix, (uint32_t)a.idx.slack,
+                           (uint32_t)a.nf, a.rates, a.F[0], a.F[1], a.F[2], FIELD ? a.field : nullptr, a.scale,
+                           a.inv_scale, a.partials, a.prev_partials, a.ring, a.ctr, ZH ? a.drho_in : 0.f,
+                           ZH ? a.drho_out : 0.f);
+        return hipGetLastError();
+    }
+};
+struct RunSteps {
+    int steps;
+    void* second;      // ping-pong: where the odd steps write
+    int64_t stride;    // else bytes between the states written, from a.dst on
+    uint32_t* sync;
+    template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
+    hipError_t run(const StepLaunch& a, Ix ix, hipStream_t s) const {
+        StepsArgs k{};
+        k.first = a.src;
+        k.out[0] = a.dst;
+        k.out[1] = second;
+        k.stride = stride;
+        k.field = FIELD ? a.field : nullptr;
+        k.partials = a.partials;
+        k.ring = a.ring;
+        k.ctr = a.ctr;
+        k.sync = sync;
+        k.slack = (uint32_t)a.idx.slack;
+        k.nf = (uint32_t)a.nf;
+        k.steps = (uint32_t)steps;
+        k.r = a.rates;
+        for (int d = 0; d < 3; ++d) k.F[d] = a.F[d];
+        k.scale = a.scale;
+        k.inv = a.inv_scale;
+        k.drho_in = ZH ? a.drho_in : 0.f;
+        k.drho_out = ZH ? a.drho_out : 0.f;
+        hipLaunchKernelGGL((k_steps<C, Ix, FIELD, TRT, FW, ZH, SYM>),
+                           dim3((unsigned)((a.nf + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, k, ix);
+        return hipGetLastError();
+    }
+};
+struct AskSteps {
+    int* blocks_per_cu;
+    template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
+    hipError_t run(const StepLaunch&, Ix, hipStream_t) const {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            blocks_per_cu, reinterpret_cast<const void*>(&k_steps<C, Ix, FIELD, TRT, FW, ZH, SYM>), kThreads, 0);
+    }
+};
 
 // Zou-He pressure faces are built for FP32 storage, the bitmap index, a
 // uniform (zero) force and halfway bounce-back; full-way bounce-back for FP32
 // storage; symmetry planes for FP32 storage and the bitmap index, without
 // pressure faces.
-template <class C, class Ix, bool TRT>
-hipError_t step_with(const StepLaunch& a, Ix ix, hipStream_t s) {
+template <class C, class Ix, bool TRT, class Op>
+hipError_t step_with(const StepLaunch& a, Ix ix, hipStream_t s, const Op& op) {
     if (a.pressure) {
         if constexpr (std::is_same<C, CodecF32>::value && std::is_same<Ix, BitmapIdx>::value) {
-            if (!a.fullway && !a.field && !a.idx.sym)
-                return step_stores<C, Ix, false, TRT, false, true, false>(a, ix, s);
+            if (!a.fullway && !a.field && !a.idx.sym) return op.template run<C, Ix, false, TRT, false, true, false>(a, ix, s);
         }
         return hipErrorInvalidValue;
     }
+    auto field = [&](auto fw, auto sym) {
+        constexpr bool FW = decltype(fw)::value, SYM = decltype(sym)::value;
+        if (a.field) return op.template run<C, Ix, true, TRT, FW, false, SYM>(a, ix, s);
+        return op.template run<C, Ix, false, TRT, FW, false, SYM>(a, ix, s);
+    };
     if (a.idx.sym) {
         if constexpr (std::is_same<C, CodecF32>::value && std::is_same<Ix, BitmapIdx>::value) {
-            if (a.fullway) return step_launch<C, Ix, TRT, true, true>(a, ix, s);
-            return step_launch<C, Ix, TRT, false, true>(a, ix, s);
+            if (a.fullway) return field(std::true_type{}, std::true_type{});
+            return field(std::false_type{}, std::true_type{});
         }
         return hipErrorInvalidValue;
     }
     if constexpr (std::is_same<C, CodecF32>::value) {
-        if (a.fullway) return step_launch<C, Ix, TRT, true>(a, ix, s);
+        if (a.fullway) return field(std::true_type{}, std::false_type{});
     } else {
         if (a.fullway) return hipErrorInvalidValue;
     }
-    return step_launch<C, Ix, TRT, false>(a, ix, s);
+    return field(std::false_type{}, std::false_type{});
 }
 
-template <class C, bool TRT>
-hipError_t step_codec(const StepLaunch& a, hipStream_t s) {
-    if (a.idx.kind == kTable) return step_with<C, TableIdx, TRT>(a, table_view(a.idx), s);
-    return step_with<C, BitmapIdx, TRT>(a, bitmap_view(a.idx), s);
+template <class C, bool TRT, class Op>
+hipError_t step_codec(const StepLaunch& a, hipStream_t s, const Op& op) {
+    if (a.idx.kind == kTable) return step_with<C, TableIdx, TRT>(a, table_view(a.idx), s, op);
+    return step_with<C, BitmapIdx, TRT>(a, bitmap_view(a.idx), s, op);
 }
 
-template <bool TRT>
-hipError_t step_collision(const StepLaunch& a, hipStream_t s) {
+template <bool TRT, class Op>
+hipError_t step_collision(const StepLaunch& a, hipStream_t s, const Op& op) {
     switch (a.storage) {
-        case kF32: return step_codec<CodecF32, TRT>(a, s);
-        case kF16: return step_codec<CodecF16, TRT>(a, s);
-        case kBF16: return step_codec<CodecBF16, TRT>(a, s);
-        case kF16R: return step_codec<CodecF16R, TRT>(a, s);
+        case kF32: return step_codec<CodecF32, TRT>(a, s, op);
+        case kF16: return step_codec<CodecF16, TRT>(a, s, op);
+        case kBF16: return step_codec<CodecBF16, TRT>(a, s, op);
+        case kF16R: return step_codec<CodecF16R, TRT>(a, s, op);
     }
     return hipErrorInvalidValue;
+}
+template <class Op>
+hipError_t step_dispatch(const StepLaunch& a, hipStream_t s, const Op& op) {
+    return a.collision == kTrt ? step_collision<true>(a, s, op) : step_collision<false>(a, s, op);
 }
 
 template <class Ix, bool CACHED, bool FIELD>
@@ -1469,8 +1851,14 @@ hipError_t static_scratch(void** ptr) {
     return hipSuccess;
 }
 
-hipError_t launch_step(const StepLaunch& a, hipStream_t s) {
-    return a.collision == kTrt ? step_collision<true>(a, s) : step_collision<false>(a, s);
+hipError_t launch_step(const StepLaunch& a, hipStream_t s) { return step_dispatch(a, s, RunStep{}); }
+
+hipError_t launch_steps(const StepLaunch& a, int steps, void* second, int64_t stride, uint32_t* sync, hipStream_t s) {
+    return step_dispatch(a, s, RunSteps{steps, second, stride, sync});
+}
+
+hipError_t steps_occupancy(const StepLaunch& a, int* blocks_per_cu) {
+    return step_dispatch(a, nullptr, AskSteps{blocks_per_cu});
 }
 
 hipError_t step_occupancy(int storage, int index_kind, int collision, int* blocks_per_cu) {
