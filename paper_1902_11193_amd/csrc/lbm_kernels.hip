@@ -84,15 +84,13 @@ struct CodecF16 {
     static __device__ __forceinline__ float cvt(T v, float inv) { return (float)v * inv; }
     static __device__ __forceinline__ T enc(float v, float s) { return (_Float16)(v * s); }
 };
-struct CodecBF16 {
+struct CodecBF16 {  // never scaled (its exponent is 0)
     using T = uint16_t;
     static constexpr int kSlots = 19;
     static constexpr bool kRef = false;
-    static __device__ __forceinline__ float cvt(T v, float inv) {
-        return __uint_as_float((uint32_t)v << 16) * inv;
-    }
+    static __device__ __forceinline__ float cvt(T v, float) { return __uint_as_float((uint32_t)v << 16); }
     // round to nearest even (NaN stays NaN): one hardware conversion on gfx950
-    static __device__ __forceinline__ T enc(float v, float s) { return __builtin_bit_cast(T, (__bf16)(v * s)); }
+    static __device__ __forceinline__ T enc(float v, float) { return __builtin_bit_cast(T, (__bf16)v); }
 };
 
 // FP16 relative to a per-node reference density: a node stores, besides its
@@ -582,44 +580,45 @@ struct BitmapIdx {
     }
 
     // F16R: the references of the nodes a step pulls from.  The sources in
-    // one row are voxels x - 1 .. x + 1, nodes r0 - 1 .. r0 + 1 (node numbers
-    // run along a row), so one 8-byte window of the reference array per row,
-    // starting at the even node (r0 - 1) & ~1 (4-byte aligned), holds them:
-    // nine loads instead of nineteen.  Across the periodic x wrap (x = 0 or
+    // one row are voxels x - 1 .. x + 1, nodes r0 - 1, r0 and r0 + (voxel x of
+    // the row is fluid) (node numbers run along a row), so one 8-byte window of
+    // the reference array per row, starting at the even node (r0 - 1) & ~1
+    // (4-byte aligned; -2 for r0 = 0, the last bytes of the chunks before the
+    // array), holds them: nine loads instead of nineteen.  One 32-bit shift by
+    // the parity of r0 + 1 puts nodes r0 - 1 and r0 into the halves of a
+    // register and one more r0 + 1 behind them; the halves are picked without
+    // any position per direction (512^3 rock: 0.772 ms with a 64-bit word of
+    // positions and 64-bit shifts, 0.746).  Across the periodic x wrap (x = 0 or
     // nx - 1) the source at x -/+ 1 is the row's last / first node, outside the
     // window; issue_refs fetches those few separately.
     struct RefPlan {
-        uint32_t ro[9];  // byte offset of each row's window in the reference array
-        uint64_t pos;    // bits 2i, 2i + 1: position of value i's source node in its row's window
-        uint32_t xw;     // bit 0: x == 0, bit 1: x == nx - 1, with nx >= 3 (sources across the wrap)
+        uint32_t t[9];  // 2 (r0 + 1) of each row: its window is at byte t & ~3 past entry -2, bit 1 the parity
+        uint32_t b;     // bit R: voxel x of row R is fluid (rows 1 .. 4)
+        uint32_t xw;    // bit 0: x == 0, bit 1: x == nx - 1, with nx >= 3 (sources across the wrap)
     };
     template <class T, int S>
     __device__ __forceinline__ void offsets_ref(const Raw& r, Pre c, uint32_t n, uint32_t chunk, uint32_t slack,
                                                 uint32_t off[19], uint32_t& wb, RefPlan& plan) const {
         constexpr uint32_t sz = sizeof(T);
+        static_assert(sz == 2, "references are 16-bit");
         const uint32_t kb = chunk_kb<T, S>(chunk, slack);
         const uint32_t ekb = node_elem<S>(n) * sz + kb;
         off[0] = ekb;
-        uint32_t walls = 0, e[9];
-        uint64_t pos = 0;
+        uint32_t walls = 0, b = 0;
         visit(r, c, [&](auto I, const Row3& w, int which) {
             constexpr int i = decltype(I)::value;
             constexpr int R = row_of(i);
             const uint32_t fluid = src_fluid(w, which);
-            const uint32_t node = src_node(w, which);
-            const uint32_t pulled = node_elem<S>(node) * sz + (kb + (uint32_t)i * kThreads * sz);
+            const uint32_t pulled = node_elem<S>(src_node(w, which)) * sz + (kb + (uint32_t)i * kThreads * sz);
             off[i] = bit_select(fluid, pulled, ekb + (uint32_t)opp(i) * kThreads * sz);
             walls |= ~fluid & (1u << i);
             if constexpr (i == 1 || i == 3 || i == 4 || i == 5 || i == 6 || i >= 15) {  // first visit of row R
-                const uint32_t r0 = (uint32_t)w.r0;
-                e[R] = (r0 == 0u ? 0u : r0 - 1u) & ~1u;
-                plan.ro[R] = e[R] * sz;
+                plan.t[R] = (uint32_t)w.r0 * 2u + 2u;
+                if constexpr (R >= 1 && R <= 4) b |= ((w.bits >> 1) & 1u) << R;
             }
-            pos |= (uint64_t)((node - e[R]) & 3u) << (2 * i);
         });
-        pos |= (uint64_t)((n - e[0]) & 3u);   // the node itself, in its own row's window
         wb = walls;
-        plan.pos = pos;
+        plan.b = b;
         // one or two voxels per row: the wrapped sources are the node itself
         // or its neighbour, inside the window
         const uint32_t x = c & ((1u << bx) - 1u);
@@ -630,7 +629,7 @@ struct BitmapIdx {
     // from, its own at a wall (finish_refs, with node n's plan and walls).
     template <class T>
     struct RefLoads {
-        uint64_t win[9];
+        uint32_t lo[9], hi[9];
         T wrap[5];  // across the x wrap: sources of c_x = +1 (x = 0) or c_x = -1 (x = nx - 1)
     };
     template <class M, class T, int S>
@@ -639,8 +638,9 @@ struct BitmapIdx {
         unroll<9>([&](auto k) {
             constexpr int R = decltype(k)::value;
             uint32_t v[2];
-            M::ld2(reinterpret_cast<const uint32_t*>(rb), plan.ro[R], v);
-            L.win[R] = (uint64_t)v[0] | ((uint64_t)v[1] << 32);
+            M::ld2(reinterpret_cast<const uint32_t*>(rb) - 1, plan.t[R] & ~3u, v);
+            L.lo[R] = v[0];
+            L.hi[R] = v[1];
         });
         if (plan.xw) {
             // Node m of a pulled value i from its offset: the load reads element
@@ -664,22 +664,43 @@ struct BitmapIdx {
     template <class T>
     __device__ __forceinline__ void finish_refs(const RefPlan& plan, uint32_t wb, const RefLoads<T>& L,
                                                 T rr[19]) const {
-        auto pick = [&](int R, int i) -> T {
-            const uint32_t q = (uint32_t)(plan.pos >> (2 * i)) & 3u;
-            return __builtin_bit_cast(T, (uint16_t)(L.win[R] >> (16u * q)));
-        };
-        const T own = pick(0, 0);
-        rr[0] = own;
+        // per row: nodes r0 - 1 (low half) and r0 (high half), and node r0 + 1 (low half)
+        uint32_t two[9], next[5];
+        unroll<9>([&](auto k) {
+            constexpr int R = decltype(k)::value;
+            const uint32_t sh = plan.t[R] << 3;  // 16 (parity) modulo 32
+            two[R] = __builtin_amdgcn_alignbit(L.hi[R], L.lo[R], sh);
+            if constexpr (R <= 4) {
+                next[R] = L.hi[R] >> (sh & 31u);
+                // voxel x solid: the node after voxel x is r0
+                if constexpr (R >= 1)
+                    next[R] = bit_select((uint32_t)__builtin_amdgcn_sbfe((int32_t)plan.b, R, 1u), next[R],
+                                         two[R] >> 16);
+            }
+        });
+        const uint32_t own = two[0] >> 16, own2 = own | two[0] & 0xffff0000u;
+        rr[0] = __builtin_bit_cast(T, (uint16_t)own);
+        uint32_t v[19];
         unroll<18>([&](auto k) {
             constexpr int i = decltype(k)::value + 1;
-            T v = pick(row_of(i), i);
-            if constexpr (i <= 14 && i != 3 && i != 4 && i != 5 && i != 6) {
-                // the x-wrapped sources
-                constexpr int slot = i <= 2 ? 0 : (i - 5) / 2;
-                constexpr unsigned side = (i & 1) ? 1u : 2u;
-                if (plan.xw == side) v = L.wrap[slot];
-            }
-            rr[i] = ((wb >> i) & 1u) ? own : v;
+            v[i] = which_of(i) > 0 ? next[row_of(i)] : two[row_of(i)];
+        });
+        if (plan.xw) {  // the x-wrapped sources: slot 0 of directions 1 and 2, then 7 .. 14
+            unroll<5>([&](auto k) {
+                constexpr int slot = decltype(k)::value;
+                constexpr int il = slot == 0 ? 1 : 2 * slot + 5, ir = il + 1;
+                const uint32_t w = __builtin_bit_cast(uint16_t, L.wrap[slot]);
+                if (plan.xw == 1u)
+                    v[il] = w;
+                else
+                    v[ir] = w;
+            });
+        }
+        unroll<18>([&](auto k) {
+            constexpr int i = decltype(k)::value + 1;
+            const uint32_t wall = (uint32_t)__builtin_amdgcn_sbfe((int32_t)wb, (uint32_t)i, 1u);
+            const uint32_t s = bit_select(wall, own2, v[i]);
+            rr[i] = __builtin_bit_cast(T, (uint16_t)(which_of(i) == 0 ? s >> 16 : s));
         });
     }
 };
@@ -1189,8 +1210,8 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
 // not promise (other kernels may hold the GPU, other launches like this one
 // wait for room too).  So the blocks first count themselves in (sync[0]).  If
 // one has waited kMeetTicks (sync[2] where that is set) and they are not all
-// there, it closes the count
-// and takes all steps of all chunks by itself; every other block then leaves.
+// there, it closes the count and takes all steps of all chunks by itself;
+// every other block then leaves.
 // The count decides once, atomically, so either all blocks run together or
 // one runs alone, and no block waits for one that may not come.
 //
