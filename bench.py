@@ -49,8 +49,9 @@ def index_bytes(index: str, shape, nf: int) -> float:
 ADJ_POP_BYTES = 3 * 19 * 4
 ADJ_ACC_BYTES = 2 * 3 * 4
 ADJ_ALG_BYTES = ADJ_POP_BYTES + ADJ_ACC_BYTES
-# The reverse sweep also recomputes the states inside each checkpoint segment:
-# K - 1 forward steps per segment of K reverse steps, 152 B per node each.
+# The reverse sweep also recomputes the states inside each checkpoint segment
+# but the last, which the forward run leaves in place: K - 1 forward steps per
+# segment of K reverse steps, 152 B per node each.
 
 
 def kernel_source_hash() -> str:
@@ -124,7 +125,7 @@ def run_adjoint(P, mask, args, N=None, K=None, g=None, label="grf_512"):
     (252 algorithmic bytes per node, 240 on the first step of a segment; the
     fraction over the 228 population bytes alone beside it) and that of the
     reverse sweep with its recompute (a 152-byte forward step per node for all
-    but one of a segment's reverse steps)."""
+    but one of a segment's reverse steps, in every segment but the last)."""
     import torch
 
     N = N or args.adj_steps
@@ -158,7 +159,7 @@ def run_adjoint(P, mask, args, N=None, K=None, g=None, label="grf_512"):
                                algorithmic_bytes_per_launch=per_node * nf,
                                frac_population_bytes=ADJ_POP_BYTES * nf / rev_s / 1e9 / HBM_PEAK_GBS)
         both = (ph["reverse_ms"] + ph["recompute_ms"]) * 1e-3
-        sweep = per_node * nrev + 2 * 19 * 4 * (nrev - segments)   # bytes per node: reverse steps + recompute steps
+        sweep = per_node * nrev + 2 * 19 * 4 * (segments - 1) * (K - 1)   # bytes per node: reverse + recompute steps
         ach2 = sweep * nf / both / 1e9
         out["roofline_with_recompute"] = dict(bound="hbm", achieved=ach2, peak=HBM_PEAK_GBS, unit="GB/s",
                                               frac=ach2 / HBM_PEAK_GBS, bytes_per_node_step=sweep / nrev)

@@ -373,7 +373,8 @@ int lbm_set_storage_exponent(lbm_ctx* ctx, int e);
  * along the largest |g| component) with respect to tau, Lambda and the
  * per-node body-force acceleration, by reverse time stepping with
  * two-level checkpointing: a snapshot every `checkpoint_every` steps, the
- * steps of one segment recomputed and kept while it is reversed.
+ * steps of one segment recomputed and kept while it is reversed (those of the
+ * last segment kept by the forward run).
  * Re-runs the forward from rest; the context's state afterwards is the
  * state after n_steps steps.  Needs FP32 storage.
  * Workspace: size from lbm_adjoint_workspace_query, device, caller-owned.

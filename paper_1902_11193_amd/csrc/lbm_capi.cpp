@@ -446,6 +446,17 @@ hipError_t run_steps(lbm_ctx* c, const lbm::StepLaunch& a, int steps, void* seco
     return he;
 }
 
+// One counted step from `src` to `dst`.
+hipError_t one_step(lbm_ctx* c, const void* src, void* dst, bool cached) {
+    const int64_t t = c->steps;
+    const double* prev = c->pending ? c->partials[(t - 1) & 1] : nullptr;
+    const hipError_t he = step_raw(c, src, dst, c->partials[t & 1], prev, c->stream, cached);
+    if (he != hipSuccess) return he;
+    ++c->steps;
+    c->pending = true;
+    return hipSuccess;
+}
+
 int do_steps(lbm_ctx* c, int n) {
     int k = 0;
     while (k < n) {
@@ -469,12 +480,8 @@ int do_steps(lbm_ctx* c, int n) {
             }
             c->graphs = false;  // capture not available: plain launches from here on
         }
-        const int64_t t = c->steps;
-        const double* prev = c->pending ? c->partials[(t - 1) & 1] : nullptr;
-        HIP_TRY(step_raw(c, c->cur, c->nxt, c->partials[t & 1], prev, c->stream, c->cached));
+        HIP_TRY(one_step(c, c->cur, c->nxt, c->cached));
         std::swap(c->cur, c->nxt);
-        ++c->steps;
-        c->pending = true;
         ++k;
     }
     return LBM_OK;
@@ -1261,14 +1268,45 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     HIP_TRY(zero_ring(c));
     c->steps = 0;
     c->pending = false;
-    for (int n = 0; n < N;) {
+    const int nrev = N - 1;                            // reverse steps n = N-1 .. 1
+    const int segs = (nrev + K - 1) / K;               // segments s: reverse steps sK+1 .. min((s+1)K, nrev)
+    const int last0 = segs > 0 ? (segs - 1) * K : N;   // the last one starts from fh^{last0}
+    for (int n = 0; n < std::min(N, last0 + 1);) {
         if (n % K == 0 && n / K < A.nsnap)
             HIP_TRY(hipMemcpyAsync(snap(n / K), c->cur, (size_t)19 * c->np * 4,
                                    hipMemcpyDeviceToDevice, c->stream));
+        if (n == last0) break;
         const int run = std::min(K - n % K, N - n);  // to the next snapshot
         int rc = do_steps(c, run);
         if (rc) return rc;
         n += run;
+    }
+    // The reverse sweep starts with the last segment, so the forward run leaves
+    // that segment's states where it reads them, and only the others are
+    // recomputed: fh^{last0+1} .. fh^{N-2} in the segment store, fh^{N-1} and
+    // fh^N in the context's buffers.  (320^3 rock, 40 steps, a checkpoint every
+    // 20: 27.7 -> 24.4 ms; 128^3 pack, 400 steps, every 40: 39.6 -> 38.7.)
+    const bool adj_cached = adjoint_bytes(c) <= kCacheBytes;
+    if (segs > 0) {
+        const void* at = c->cur;
+        for (int n = last0; n < nrev - 1;) {
+            const int run = std::min(nrev - 1 - n, steps_per_launch(c));
+            if (run >= kStepsLeast && several_steps(c)) {
+                int rc = flush(c);
+                if (rc) return rc;
+                HIP_TRY(run_steps(c, step_args(c, at, seg(n + 1 - last0), c->partials[0]), run, nullptr,
+                                  (int64_t)state));
+                c->steps += run;
+                n += run;
+            } else {
+                HIP_TRY(one_step(c, at, seg(n + 1 - last0), adj_cached));
+                ++n;
+            }
+            at = seg(n - last0);
+        }
+        // fh^{N-1} and fh^N
+        HIP_TRY(one_step(c, at, c->nxt, c->cached));
+        HIP_TRY(one_step(c, c->nxt, c->cur, c->cached));
     }
     HIP_TRY(timer.mark(kPhaseOther, c->stream));
     double u[3];
@@ -1296,16 +1334,15 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     // stores and one from HBM (us per adjoint step, 1 / 2 blocks: 128^3 rock,
     // cached 63.1 / 58.3, streaming 64.3 / 62.5; 160^3, 206 MB, 103.2 / 100.5
     // and 103.8 / 104.3; 192^3, 350 MB, 168.5 / 171.0 and 162.7 / 165.8).
-    al.cached = adjoint_bytes(c) <= kCacheBytes;
+    al.cached = adj_cached;
     al.grid = (int)std::min<int64_t>(c->np / lbm::kChunk, (int64_t)std::max(c->cus, 1) * (al.cached ? 2 : 1));
     al.partials = part6;
-    const int nrev = N - 1;  // reverse steps n = N-1 .. 1
-    for (int s = (nrev + K - 1) / K - 1; s >= 0; --s) {
+    for (int s = segs - 1; s >= 0; --s) {
         const int n0 = s * K;                        // segment start: fh^{n0}
         const int n1 = std::min((s + 1) * K, nrev);  // last reverse step of the segment
         // recompute fh^{n0+1} .. fh^{n1-1}
         HIP_TRY(timer.mark(kPhaseRecompute, c->stream));
-        for (int t = 1; t < n1 - n0;) {
+        for (int t = 1; t < n1 - n0 && s < segs - 1;) {
             const void* src = t == 1 ? (const void*)snap(s) : (const void*)seg(t - 1);
             const int run = std::min(n1 - n0 - t, kStepsMost);
             if (run >= kStepsLeast && several_steps(c)) {
