@@ -341,7 +341,11 @@ bool several_steps(lbm_ctx* c) {
     if (!c->graphs || chunks > kStepsChunks) return false;
     // a captured launch may be replayed beside any other
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
     if (c->steps_fit < 0) {
         int per_cu = 0;
         const hipError_t he = lbm::steps_occupancy(step_args(c, c->cur, c->nxt, c->partials[0]), &per_cu);
@@ -350,10 +354,6 @@ bool several_steps(lbm_ctx* c) {
     return chunks <= c->steps_fit;
 }
 
-// Step n (0-based) writes partials[n % 2]; its launch also reduces the
-// partials of step n-1 into the ring.  With a step pending, runs of
-// kGraphSteps steps replay a captured graph (one launch call instead of
-// kGraphSteps; the launches and their arguments are the same).
 int flush(lbm_ctx* c);
 
 // Launches of several steps need all their blocks running at once, so those of
@@ -362,8 +362,8 @@ int flush(lbm_ctx* c);
 // event recorded behind it.  With one stream (the usual case) nothing is
 // recorded, as its launches follow each other.  With more, a launch that does
 // not fit beside those still in flight waits, on the GPU, for the oldest of
-// them.  The kernel
-// itself stays correct where it does not get its room (k_steps).
+// them.  The kernel itself stays correct where it does not get its room
+// (k_steps).
 struct StepsInFlight {
     int contexts = 0;
     hipEvent_t event = nullptr;
@@ -372,7 +372,8 @@ struct StepsInFlight {
 };
 std::mutex g_steps_mu;
 uint64_t g_launch = 1;
-std::map<std::pair<int, hipStream_t>, StepsInFlight> g_steps;   // by device and stream
+// by device and stream; never destroyed, as contexts may outlive static objects
+auto& g_steps = *new std::map<std::pair<int, hipStream_t>, StepsInFlight>;
 
 // A second stream on the GPU: what the first has in flight was not recorded.
 void record_first(int dev) {
@@ -384,13 +385,16 @@ void record_first(int dev) {
             first = &s;
             stream = key.second;
         }
+    if (!first) return;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!first || hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
-    if (!first->event && hipEventCreateWithFlags(&first->event, hipEventDisableTiming) != hipSuccess) {
-        first->event = nullptr;
-        return;
-    }
-    if (hipEventRecord(first->event, stream) == hipSuccess) first->share = 1.0;
+    hipError_t he = hipStreamIsCapturing(stream, &cap);
+    if (he == hipSuccess && cap != hipStreamCaptureStatusNone) return;
+    if (he == hipSuccess && !first->event) he = hipEventCreateWithFlags(&first->event, hipEventDisableTiming);
+    if (he == hipSuccess) he = hipEventRecord(first->event, stream);
+    if (he == hipSuccess)
+        first->share = 1.0;
+    else
+        (void)hipGetLastError();
 }
 void steps_register(lbm_ctx* c) {
     std::lock_guard<std::mutex> lock(g_steps_mu);
@@ -457,6 +461,11 @@ hipError_t one_step(lbm_ctx* c, const void* src, void* dst, bool cached) {
     return hipSuccess;
 }
 
+// Small images take several steps a launch (several_steps).  Otherwise step n
+// (0-based) writes partials[n % 2]; its launch also reduces the partials of
+// step n-1 into the ring.  With a step pending, runs of kGraphSteps steps
+// replay a captured graph (one launch call instead of kGraphSteps; the
+// launches and their arguments are the same).
 int do_steps(lbm_ctx* c, int n) {
     int k = 0;
     while (k < n) {

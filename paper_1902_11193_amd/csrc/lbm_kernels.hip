@@ -1039,7 +1039,8 @@ __device__ __forceinline__ Moved collide_node(float f[19], uint32_t n, uint32_t 
 // knows each node's x).  SYM: symmetry planes on the y / z faces (bitmap
 // index, BitmapIdx::offsets).
 // The plain MRT step fits 96 VGPRs without spilling, so 5 blocks of it fit a
-// CU, which the 16-bit storages use (FP32 storage launches one block per CU);
+// CU, which the 16-bit storages use (FP32 storage past a few chunks per CU
+// launches one or two);
 // the reference-density, link-wise TRT, full-way and symmetry variants would
 // spill there and keep the compiler's choice.
 template <class C, class Ix, bool CACHED, bool FIELD, bool TRT, bool FW, bool ZH = false, bool SYM = false>
@@ -1215,11 +1216,10 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
 // The count decides once, atomically, so either all blocks run together or
 // one runs alone, and no block waits for one that may not come.
 //
-// State t of the launch is read from `first` (t = 0) or written by step t - 1
-// to out + ((t - 1) % 2) * stride (ping-pong) or out + (t - 1) * stride.
+// Step t reads `first` (t = 0) or what step t - 1 wrote.
 struct StepsArgs {
     const void* first;    // state before the first step
-    void* out[2];         // where steps 0, 2, ... and 1, 3, ... write (PING), else out[0] + t * stride
+    void* out[2];         // where steps 0, 2, ... and 1, 3, ... write; with a stride out[0] + t * stride
     int64_t stride;       // bytes between successive states; 0: ping-pong between out[0] and out[1]
     const float* field;
     double* partials;     // [steps][gridDim.x][4], or nullptr: no sums wanted
@@ -1513,9 +1513,9 @@ __device__ __forceinline__ Vec3 gquad(float vx, float vy, float vz, const Mom& w
 // touched once per step, so it is read and written with non-temporal
 // accesses that leave L2 to the gathered lines.  Software pipeline as in
 // k_step: the index entries of the next node are loaded and decoded while
-// this node's 38 gathers are in flight.  It is launched with one block per
-// compute unit (its two gathered arrays make it bound by L2 misses, not by
-// latency), where the registers this pipeline needs (151) cost no occupancy.
+// this node's 38 gathers are in flight.  It is launched with one or two blocks
+// per compute unit, where the registers this pipeline needs (145) cost no
+// occupancy.
 // Tail lanes as in k_step: lanes past the list load node nf - 1 and store to
 // their own padded slots.
 template <class Ix, bool CACHED, bool FIELD>
