@@ -302,6 +302,11 @@ size_t adjoint_bytes(const lbm_ctx* c) {
 // the narrowest window keeps to the fewest DRAM pages (512^3 0.738 / 0.840 ms).
 constexpr size_t kCacheBytes = (size_t)256 << 20;
 constexpr size_t kTwoBlockBytes = (size_t)160 << 20;
+// 16-bit states of a few MB stay in L2 whole, and what is dirty there is
+// written back after the last block (FP16, us per step streaming / plain: a
+// rock of 1,407 chunks, 33 MB, 13.1 / 13.6, a bore of 1,649 chunks 14.2 /
+// 14.6; 192^3 rock, 122 MB, 35.4 / 30.9).
+constexpr size_t kCacheLeast16 = (size_t)48 << 20;
 hipError_t choose_launch(lbm_ctx* c) {
     int per_cu = 0;
     hipError_t he = lbm::step_occupancy(c->storage, c->index_kind, c->collision, &per_cu);
@@ -311,7 +316,7 @@ hipError_t choose_launch(lbm_ctx* c) {
     const size_t bytes = step_bytes(c);
     if (c->storage == LBM_F32 && chunks > cus * per_cu) per_cu = bytes <= kTwoBlockBytes ? std::min(per_cu, 2) : 1;
     c->grid = (int)std::min<int64_t>({chunks, cus * per_cu, (int64_t)kMaxGrid});
-    c->cached = bytes <= kCacheBytes;
+    c->cached = bytes <= kCacheBytes && (c->storage == LBM_F32 || bytes >= kCacheLeast16);
     return hipSuccess;
 }
 
