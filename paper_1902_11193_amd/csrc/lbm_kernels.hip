@@ -589,12 +589,13 @@ struct BitmapIdx {
     // register and one more r0 + 1 behind them; the halves are picked without
     // any position per direction (512^3 rock: 0.772 ms with a 64-bit word of
     // positions and 64-bit shifts, 0.746).  Across the periodic x wrap (x = 0 or
-    // nx - 1) the source at x -/+ 1 is the row's last / first node, outside the
-    // window; issue_refs fetches those few separately.
+    // nx - 1) the source at x -/+ 1 is the row's last / first node, not the one
+    // beside r0; issue_refs fetches those few separately, one per row.  In rows
+    // of one voxel both wraps lead to the same node.
     struct RefPlan {
         uint32_t t[9];  // 2 (r0 + 1) of each row: its window is at byte t & ~3 past entry -2, bit 1 the parity
         uint32_t b;     // bit R: voxel x of row R is fluid (rows 1 .. 4)
-        uint32_t xw;    // bit 0: x == 0, bit 1: x == nx - 1, with nx >= 3 (sources across the wrap)
+        uint32_t xw;    // bit 0: x == 0, bit 1: x == nx - 1 (sources across the wrap)
     };
     template <class T, int S>
     __device__ __forceinline__ void offsets_ref(const Raw& r, Pre c, uint32_t n, uint32_t chunk, uint32_t slack,
@@ -619,10 +620,8 @@ struct BitmapIdx {
         });
         wb = walls;
         plan.b = b;
-        // one or two voxels per row: the wrapped sources are the node itself
-        // or its neighbour, inside the window
         const uint32_t x = c & ((1u << bx) - 1u);
-        plan.xw = nx < 3 ? 0u : (x == 0 ? 1u : (x == nx - 1 ? 2u : 0u));
+        plan.xw = (x == 0 ? 1u : 0u) | (x == nx - 1 ? 2u : 0u);
     }
     // Loads in flight for node n (issue_refs, before the next node's offsets
     // overwrite the plan), then rr[i] = reference of the node value i came
@@ -630,8 +629,14 @@ struct BitmapIdx {
     template <class T>
     struct RefLoads {
         uint32_t lo[9], hi[9];
-        T wrap[5];  // across the x wrap: sources of c_x = +1 (x = 0) or c_x = -1 (x = nx - 1)
+        T wrap[5];  // across the x wrap: rows 0 .. 4's sources of c_x = +1 (x = 0) or c_x = -1 (x = nx - 1)
     };
+    // the direction that pulls from voxel x + which of row R (which = -1, +1)
+    static __host__ __device__ constexpr int wrap_dir(int R, int which) {
+        for (int i = 1; i < 19; ++i)
+            if (row_of(i) == R && which_of(i) == which) return i;
+        return -1;
+    }
     template <class M, class T, int S>
     __device__ __forceinline__ void issue_refs(const RefPlan& plan, const T* rb, uint32_t wb, const uint32_t* off,
                                                uint32_t chunk, uint32_t slack, RefLoads<T>& L) const {
@@ -648,8 +653,7 @@ struct BitmapIdx {
             // states pass 4 GiB), which is node_elem(m) + i * 256.
             const bool left = plan.xw & 1u;  // x = 0: c_x = +1 pulls the row's last node
             unroll<5>([&](auto k) {
-                constexpr int a = 2 * decltype(k)::value + 1;          // 1, 7, 9, 11, 13 ...
-                constexpr int il = a == 1 ? 1 : a + 4, ir = il + 1;    // ... and 2, 8, 10, 12, 14
+                constexpr int il = wrap_dir(decltype(k)::value, -1), ir = wrap_dir(decltype(k)::value, 1);
                 const int i = left ? il : ir;
                 if (!((wb >> i) & 1u)) {
                     const uint32_t o = left ? off[il] : off[ir];
@@ -685,15 +689,12 @@ struct BitmapIdx {
             constexpr int i = decltype(k)::value + 1;
             v[i] = which_of(i) > 0 ? next[row_of(i)] : two[row_of(i)];
         });
-        if (plan.xw) {  // the x-wrapped sources: slot 0 of directions 1 and 2, then 7 .. 14
+        if (plan.xw) {  // the x-wrapped sources
             unroll<5>([&](auto k) {
-                constexpr int slot = decltype(k)::value;
-                constexpr int il = slot == 0 ? 1 : 2 * slot + 5, ir = il + 1;
-                const uint32_t w = __builtin_bit_cast(uint16_t, L.wrap[slot]);
-                if (plan.xw == 1u)
-                    v[il] = w;
-                else
-                    v[ir] = w;
+                constexpr int il = wrap_dir(decltype(k)::value, -1), ir = wrap_dir(decltype(k)::value, 1);
+                const uint32_t w = __builtin_bit_cast(uint16_t, L.wrap[decltype(k)::value]);
+                if (plan.xw & 1u) v[il] = w;
+                if (plan.xw & 2u) v[ir] = w;
             });
         }
         unroll<18>([&](auto k) {
