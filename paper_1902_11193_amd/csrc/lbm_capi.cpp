@@ -332,6 +332,10 @@ bool two_rate(const lbm::RateClasses& r) {
 // packs, several / one a launch: 95 chunks 3.8 / 6.7, 261 4.8 / 8.1, 555 6.9 /
 // 10.2, 760 9.1 / 10.5, 1012 13.2 / 12.6; FP16 760 7.7 / 10.3; F16R 760 9.6 /
 // 13.0; full-way walls and mirror planes 760 9.8 / 11.5).
+// A single step of such an image has one block per chunk too, so that both
+// launches add the same block sums; where only fewer blocks of the single step
+// fit (F16R, 3 per unit: 768), the image takes single steps (F16R, several /
+// one a launch: 819 chunks 11.4 / 11.9, 880 12.5 / 12.2).
 constexpr int64_t kStepsChunks = 896;
 static_assert(kStepsChunks <= lbm::kStepsBlocks, "the barrier memory has a word per block");
 constexpr int kStepsLeast = 4;      // steps worth such a launch
@@ -343,7 +347,7 @@ int steps_per_launch(const lbm_ctx* c) {
 }
 bool several_steps(lbm_ctx* c) {
     const int64_t chunks = c->np / lbm::kChunk;
-    if (!c->graphs || chunks > kStepsChunks) return false;
+    if (!c->graphs || chunks > kStepsChunks || c->grid != chunks) return false;
     // a captured launch may be replayed beside any other
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
