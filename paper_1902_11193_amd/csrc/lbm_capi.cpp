@@ -157,6 +157,7 @@ struct lbm_ctx {
     int grid;
     bool cached;  // the step's results stay in the caches (choose_launch)
     int steps_fit;  // blocks of launch_steps that run at once with the current settings; -1: not asked yet
+    uint32_t told;  // what launch_steps has the chunks' words hold
     double* partials[2];
     double* ring;
     uint32_t* ctr;      // steps reduced into the ring so far (device, after the ring)
@@ -425,7 +426,7 @@ hipError_t run_steps(lbm_ctx* c, const lbm::StepLaunch& a, int steps, void* seco
     std::lock_guard<std::mutex> lock(g_steps_mu);
     size_t streams = 0;
     for (const auto& s : g_steps) streams += s.first.first == c->dev;
-    if (streams < 2) return lbm::launch_steps(a, steps, second, stride, sync, c->stream);
+    if (streams < 2) return lbm::launch_steps(a, steps, second, stride, sync, &c->told, c->stream);
     StepsInFlight& mine = g_steps[{c->dev, c->stream}];
     const double share = (double)(c->np / lbm::kChunk) / std::max(c->steps_fit, 1);
     double others = 0.0;
@@ -450,7 +451,7 @@ hipError_t run_steps(lbm_ctx* c, const lbm::StepLaunch& a, int steps, void* seco
         others -= oldest->share;
     }
     if (he == hipSuccess && !mine.event) he = hipEventCreateWithFlags(&mine.event, hipEventDisableTiming);
-    if (he == hipSuccess) he = lbm::launch_steps(a, steps, second, stride, sync, c->stream);
+    if (he == hipSuccess) he = lbm::launch_steps(a, steps, second, stride, sync, &c->told, c->stream);
     if (he == hipSuccess) he = hipEventRecord(mine.event, c->stream);
     if (he == hipSuccess) {
         mine.share = std::max(mine.share, share);
@@ -728,6 +729,7 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
     c->ctr = reinterpret_cast<uint32_t*>(c->ring + (size_t)kRing * 4);
     c->graphs = true;
     c->steps_fit = -1;
+    c->told = 0;
     c->cap_stream = nullptr;
     for (auto& g : c->gexec) g = nullptr;
     c->steps = 0;

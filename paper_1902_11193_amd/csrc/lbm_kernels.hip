@@ -1212,10 +1212,14 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
 // not promise (other kernels may hold the GPU, other launches like this one
 // wait for room too).  So the blocks first count themselves in (sync[0]).  If
 // one has waited kMeetTicks (sync[2] where that is set) and they are not all
-// there, it closes the count and takes all steps of all chunks by itself;
-// every other block then leaves.
-// The count decides once, atomically, so either all blocks run together or
-// one runs alone, and no block waits for one that may not come.
+// there, it closes the count, once for all of them: those that are there, and
+// those that come later, then take the chunk-steps one by one from a counter,
+// step by step.  A chunk-step waits only for ones with lower numbers, which
+// running blocks hold, so any number of blocks gets through, however late they
+// start, and all that get room take part (800 chunks, us per step: 10.2 with all
+// blocks there, 15.0 with the count closed from the start; one block for all
+// chunks takes 2985).  0.1 ms is longer than the blocks of a launch take to start
+// on a free GPU (880 chunks: with 20 us some counts are closed).
 //
 // Step t reads `first` (t = 0) or what step t - 1 wrote.
 struct StepsArgs {
@@ -1228,39 +1232,47 @@ struct StepsArgs {
     uint32_t* ctr;
     uint32_t* sync;       // kSyncBytes, zero before the first launch
     uint32_t slack, nf, steps;
+    uint32_t before;      // what every block's word holds
     RatesF r;
     float F[3], scale, inv, drho_in, drho_out;
 };
-constexpr uint32_t kClosed = 0x80000000u;   // sync[0]: the count is closed, one block runs alone
-constexpr int64_t kMeetTicks = 10000000;    // 0.1 s of the 100 MHz clock
+constexpr uint32_t kClosed = 0x80000000u;   // sync[0]: the count is closed
+constexpr int64_t kMeetTicks = 10000;       // 0.1 ms of the 100 MHz clock
 constexpr int64_t kStuckTicks = 2000000000; // 20 s: no block came (a lost GPU); sums become NaN
+// Words of sync: the count, blocks that left a closed count, kMeetTicks where
+// set (kNever: the count is closed from the start), closed counts so far, a
+// block waited in vain; on a line of its own the next chunk-step.
+constexpr uint32_t kNever = 0xffffffffu;
+constexpr uint32_t kLeft = 1, kMeetWord = 2, kClosedSoFar = 3, kLost = 4, kNext = 16;
 
 __device__ __forceinline__ uint32_t ld_sync(const uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Thread 0 of a block counts it in.  0: all blocks are here; 1: this block
-// runs alone; 2: another one does, leave.
-__device__ __forceinline__ int count_in(uint32_t* sync, uint32_t blocks) {
-    uint32_t v = __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-    const uint32_t set = ld_sync(sync + 2);
+__device__ __forceinline__ void st_sync(uint32_t* p, uint32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t add_sync(uint32_t* p) {
+    return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Thread 0 of a block counts it in.  False: the count is closed.
+__device__ __forceinline__ bool count_in(uint32_t* sync, uint32_t blocks) {
+    const uint32_t set = ld_sync(sync + kMeetWord);
+    uint32_t v = add_sync(sync) + 1u;
+    if (set == kNever) {
+        if (v == 1u) add_sync(sync + kClosedSoFar);
+        return false;
+    }
     const int64_t most = set ? (int64_t)set : kMeetTicks, t0 = wall_clock64();
     while (!(v & kClosed) && v < blocks) {
-        if (wall_clock64() - t0 > most) {
-            if (__hip_atomic_compare_exchange_strong(sync, &v, v | kClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT))
-                return 1;
-            continue;  // v holds the count as it is now
-        }
-        v = ld_sync(sync);
+        if (wall_clock64() - t0 <= most) {
+            v = ld_sync(sync);
+        } else if (__hip_atomic_compare_exchange_strong(sync, &v, v | kClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT)) {
+            add_sync(sync + kClosedSoFar);
+            return false;
+        }  // else v holds the count as it is now
     }
-    return (v & kClosed) ? 2 : 0;
-}
-// One block leaves a closed count; the last of them resets it.
-__device__ __forceinline__ void count_out(uint32_t* sync, uint32_t blocks) {
-    if (__hip_atomic_fetch_add(sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == blocks) {
-        __hip_atomic_store(sync + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(sync, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    return !(v & kClosed);
 }
 
 template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
@@ -1269,27 +1281,22 @@ k_steps(const StepsArgs a, Ix ix) {
     using T = typename C::T;
     constexpr int S = C::kSlots;
     constexpr bool REF = C::kRef;
-    __shared__ int s_word;
+    __shared__ uint32_t s_word;
+    __shared__ bool s_stuck;
     __shared__ uint32_t s_mask[kStepsBlocks / 32], s_count;
-    __shared__ uint16_t s_near[kStepsBlocks];   // the blocks this one gathers from
+    __shared__ uint16_t s_near[kStepsBlocks];   // the chunks this one gathers from
     const uint32_t G = gridDim.x;   // = chunks
-    // steps finished by block b, over all launches
-    auto done = [&](uint32_t b) { return a.sync + kSyncHead + b * kSyncStride; };
-    if (threadIdx.x == 0) s_word = count_in(a.sync, G);
-    __syncthreads();
-    const int mode = s_word;
-    __syncthreads();
-    if (mode == 2) {
-        if (threadIdx.x == 0) count_out(a.sync, G);
-        return;
+    // steps finished of chunk q, over all launches
+    auto done = [&](uint32_t q) { return a.sync + kSyncHead + q * kSyncStride; };
+    if (threadIdx.x == 0) {
+        s_stuck = false;
+        s_word = count_in(a.sync, G);
     }
-    const bool alone = mode == 1;
-    // The other blocks of a closed count change nothing but sync[0] and
-    // sync[1], so `done` and `ctr` stand still until the launch's own writes.
-    const uint32_t before = ld_sync(done(blockIdx.x));
-    const uint32_t slot0 = ld_sync(a.ctr);
+    __syncthreads();
+    const bool together = s_word != 0u;
+    const uint32_t slot0 = ld_sync(a.ctr);   // stands still until the launch's own write at its end
 
-    uint32_t c = alone ? 0u : blockIdx.x;
+    uint32_t c = blockIdx.x;
     uint32_t n, off[19], wb = 0, side = 0;
     typename Ix::RefPlan plan;
     auto place = [&] {  // the gathers of chunk c
@@ -1302,22 +1309,22 @@ k_steps(const StepsArgs a, Ix ix) {
         else
             ix.template offsets<T, S, FW, SYM>(raw, p, n, c, a.slack, off, wb);
         if constexpr (ZH) side = ix.x_face(p);
-    };
-    place();
-    if (!alone) {
-        if (threadIdx.x < kStepsBlocks / 32) s_mask[threadIdx.x] = 0u;
+        // the chunks they come from; its own as well where another block may have stepped it
+        __syncthreads();
+        if (threadIdx.x < kStepsBlocks / 32)
+            s_mask[threadIdx.x] = !together && threadIdx.x == c / 32u ? 1u << (c % 32u) : 0u;
         if (threadIdx.x == 0) s_count = 0u;
         __syncthreads();
-        unroll<18>([&](auto k) {  // the chunk each value is gathered from
+        unroll<18>([&](auto k) {
             const uint32_t q =
                 (off[decltype(k)::value + 1] / (uint32_t)sizeof(T) - a.slack + c * kChunkElems) / kChunkElems;
             if (q != c) atomicOr(&s_mask[q / 32u], 1u << (q % 32u));
         });
         __syncthreads();
-        for (uint32_t b = threadIdx.x; b < G; b += kThreads)
-            if ((s_mask[b / 32u] >> (b % 32u)) & 1u) s_near[atomicAdd(&s_count, 1u)] = (uint16_t)b;
+        for (uint32_t q = threadIdx.x; q < G; q += kThreads)
+            if ((s_mask[q / 32u] >> (q % 32u)) & 1u) s_near[atomicAdd(&s_count, 1u)] = (uint16_t)q;
         __syncthreads();
-    }
+    };
     const uint32_t so = threadIdx.x * (uint32_t)sizeof(T);
     auto step = [&](uint32_t t) {  // step t of chunk c
         auto state = [&](uint32_t k) -> T* {  // written by step k
@@ -1390,11 +1397,11 @@ k_steps(const StepsArgs a, Ix ix) {
         acc[3] += live ? (double)mv.drho : 0.0;
         block_sum<4, true>(acc, a.partials + ((size_t)t * G + c) * 4);
     };
-    // this block has finished `count` steps
+    // chunk c has had `count` steps, over all launches
     auto tell = [&](uint32_t count) {
-        if (threadIdx.x == 0) __hip_atomic_store(done(blockIdx.x), count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) st_sync(done(c), count);
     };
-    // one wave waits until the blocks which(0 .. count - 1) have finished `target` steps
+    // one wave waits until the chunks which(0 .. count - 1) have had `target` steps
     auto wait = [&](uint32_t count, auto which, uint32_t target) {
         if (threadIdx.x < 64) {
             int64_t t0 = 0;
@@ -1404,46 +1411,67 @@ k_steps(const StepsArgs a, Ix ix) {
                     if (++polls % 1024u != 0) continue;
                     if (t0 == 0) t0 = wall_clock64();
                     if (wall_clock64() - t0 > kStuckTicks) {
-                        s_word = -1;
+                        s_stuck = true;
                         break;
                     }
                 }
         }
         __syncthreads();
-        return s_word != -1;
+        return !s_stuck;
     };
+    auto near = [&](uint32_t k) { return (uint32_t)s_near[k]; };
     bool stuck = false;
-    for (uint32_t t = 0; t < a.steps && !stuck; ++t) {
-        if (alone) {
-            for (c = 0; c < G; ++c) {
-                place();
-                sum(t, step(t));
-                __syncthreads();
-            }
-            continue;
-        }
-        const Moved mv = step(t);
-        tell(before + t + 1u);
-        sum(t, mv);   // while the word travels
-        if (t + 1u < a.steps) {
-            stuck = !wait(s_count, [&](uint32_t k) { return (uint32_t)s_near[k]; }, before + t + 1u);
-        } else {      // all blocks, their sums written
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (uint32_t k = 0;; ++k) {
+        uint32_t t = k;
+        if (!together) {
             __syncthreads();
-            tell(before + t + 2u);
-            stuck = !wait(G, [&](uint32_t k) { return k; }, before + t + 2u);
+            if (threadIdx.x == 0) s_word = add_sync(a.sync + kNext);
+            __syncthreads();
+            const uint32_t q = __builtin_amdgcn_readfirstlane(s_word);
+            t = q / G;
+            c = q % G;
+        }
+        if (t >= a.steps || stuck) break;
+        if (k == 0 || !together) place();
+        // until the chunks it gathers from have had t steps; it then also
+        // overwrites nothing that they still read
+        stuck = t > 0 && !wait(s_count, near, a.before + t);
+        const Moved mv = step(t);
+        tell(a.before + t + 1u);
+        sum(t, mv);   // while the word travels
+    }
+    // all blocks, their sums written
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (together) {
+        tell(a.before + a.steps + 1u);
+        stuck = !wait(G, [&](uint32_t q) { return q; }, a.before + a.steps + 1u);
+    } else {   // the last block to leave a closed count finishes the launch
+        if (threadIdx.x == 0) {
+            if (stuck) st_sync(a.sync + kLost, 1u);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            s_word = add_sync(a.sync + kLeft) + 1u;
+        }
+        __syncthreads();
+        if (s_word != G) return;
+        stuck = ld_sync(a.sync + kLost) != 0u;
+        __syncthreads();
+        for (uint32_t q = threadIdx.x; q < G; q += kThreads) st_sync(done(q), a.before + a.steps + 1u);
+        if (threadIdx.x == 0) {
+            st_sync(a.sync + kLeft, 0u);
+            st_sync(a.sync + kLost, 0u);
+            st_sync(a.sync + kNext, 0u);
         }
     }
-    if (alone) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
     // All steps are done and their sums written: reduce them, step s by block
-    // s % G (by this one when it runs alone), or for few blocks by one wave
+    // s % G (by the last one of a closed count), or for few blocks by one wave
     // each, which adds in the order reduce_partials does.
     if (a.partials) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const uint32_t share = G <= 64 ? kThreads / 64 : 1;   // steps a block reduces at a time
-        const uint32_t s0 = (alone ? 0u : blockIdx.x) * share, ds = (alone ? 1u : G) * share;
+        const uint32_t s0 = (together ? blockIdx.x : 0u) * share, ds = (together ? G : 1u) * share;
         const uint32_t wave = threadIdx.x / 64, lane = threadIdx.x % 64;
         for (uint32_t q = s0; q < a.steps; q += ds) {
             const uint32_t s = share > 1 ? q + wave : q;
@@ -1464,11 +1492,10 @@ k_steps(const StepsArgs a, Ix ix) {
             }
         }
     }
-    if (threadIdx.x == 0 && (alone || blockIdx.x == 0)) {
+    if (threadIdx.x == 0 && (blockIdx.x == 0 || !together)) {
         if (a.partials) *a.ctr = slot0 + a.steps;
-        if (!alone) __hip_atomic_store(a.sync, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        st_sync(a.sync, 0u);
     }
-    if (alone && threadIdx.x == 0) count_out(a.sync, G);
 }
 
 __global__ void k_zero(uint32_t* p, int64_t words) {
@@ -1750,6 +1777,7 @@ struct RunSteps {
     void* second;      // ping-pong: where the odd steps write
     int64_t stride;    // else bytes between the states written, from a.dst on
     uint32_t* sync;
+    uint32_t before;
     template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
     hipError_t run(const StepLaunch& a, Ix ix, hipStream_t s) const {
         StepsArgs k{};
@@ -1762,6 +1790,7 @@ struct RunSteps {
         k.ring = a.ring;
         k.ctr = a.ctr;
         k.sync = sync;
+        k.before = before;
         k.slack = (uint32_t)a.idx.slack;
         k.nf = (uint32_t)a.nf;
         k.steps = (uint32_t)steps;
@@ -1875,8 +1904,11 @@ hipError_t static_scratch(void** ptr) {
 
 hipError_t launch_step(const StepLaunch& a, hipStream_t s) { return step_dispatch(a, s, RunStep{}); }
 
-hipError_t launch_steps(const StepLaunch& a, int steps, void* second, int64_t stride, uint32_t* sync, hipStream_t s) {
-    return step_dispatch(a, s, RunSteps{steps, second, stride, sync});
+hipError_t launch_steps(const StepLaunch& a, int steps, void* second, int64_t stride, uint32_t* sync,
+                        uint32_t* told, hipStream_t s) {
+    const hipError_t he = step_dispatch(a, s, RunSteps{steps, second, stride, sync, *told});
+    if (he == hipSuccess) *told += (uint32_t)steps + 1u;
+    return he;
 }
 
 hipError_t steps_occupancy(const StepLaunch& a, int* blocks_per_cu) {

@@ -73,22 +73,26 @@ struct StepLaunch {
 // and per-block FP64 partial sums of (ux, uy, uz, drho).
 hipError_t launch_step(const StepLaunch& a, hipStream_t s);
 
-// Words of a context's barrier memory for launch_steps: kSyncHead of the count,
-// then one per block, each in a 64-byte line of its own; zero before the first
+// Words of a context's barrier memory for launch_steps: kSyncHead of counts,
+// then one per chunk, each in a 64-byte line of its own; zero before the first
 // launch.
 constexpr int kSyncHead = 64, kSyncStride = 16;
 constexpr int kStepsBlocks = 1024;   // most blocks of such a launch
 constexpr size_t kSyncBytes = (kSyncHead + kStepsBlocks * kSyncStride) * sizeof(uint32_t);
 
 // `steps` steps in one launch of one block per chunk (at most kStepsBlocks
-// chunks, few enough to run at once; any number gives the same results).
+// chunks, few enough to run at once; fewer that do get the GPU share the work,
+// with the same results).
 // Step t reads state t: a.src for t = 0, else what step t - 1 wrote; it
 // writes a.dst and `second` in turn (stride 0, second the buffer of a.src), or
 // a.dst + t * stride bytes.  a.partials holds steps * chunks * 4 doubles, or is
 // null when no sums are wanted; the sums of all steps go into the ring and the
 // counter advances by `steps`, so nothing is pending before or after (a.grid,
 // a.prev_partials and a.cached are not read).
-hipError_t launch_steps(const StepLaunch& a, int steps, void* second, int64_t stride, uint32_t* sync, hipStream_t s);
+// *told: what the chunks' words hold once the launches so far are done (0 at
+// first), counted on by a launch.
+hipError_t launch_steps(const StepLaunch& a, int steps, void* second, int64_t stride, uint32_t* sync,
+                        uint32_t* told, hipStream_t s);
 // Blocks of that launch that fit a compute unit.
 hipError_t steps_occupancy(const StepLaunch& a, int* blocks_per_cu);
 
