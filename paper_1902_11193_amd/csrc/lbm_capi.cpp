@@ -155,7 +155,6 @@ struct lbm_ctx {
     void* nxt;
     lbm::IndexView idx;
     int grid;
-    bool cached;  // the step's results stay in the caches (choose_launch)
     int steps_fit;  // blocks of launch_steps that run at once with the current settings; -1: not asked yet
     uint32_t told;  // what launch_steps has the chunks' words hold
     double* partials[2];
@@ -166,13 +165,19 @@ struct lbm_ctx {
     const float* field;
     int exponent;
     std::vector<uint8_t> geom;
-    // captured kGraphSteps-step sequences, by (cur buffer, step parity); any
-    // change of what a step launch bakes in drops them
+    // captured kGraphSteps-step sequences, by (stores, cur buffer, step parity);
+    // any change of what a step launch bakes in drops them
     bool graphs;
     hipStream_t cap_stream;
-    hipGraphExec_t gexec[4];
+    hipGraphExec_t gexec[8];
     int dev;           // the GPU of the workspace and stream
     bool registered;   // counted in g_steps
+    // what the work it has enqueued takes of the GPU (choose), until a call of
+    // the library has seen its stream drained; in the list of live contexts
+    int64_t taken_chunks;   // of small images
+    bool taken_several;     // by launches of several steps
+    size_t taken_bytes;
+    lbm_ctx *live_prev, *live_next;
     int static_dev;  // device whose static reduction scratch this context holds, or -1
     double adj_ms[3];  // last lbm_adjoint: forward, recompute and reverse milliseconds
     bool adj_timed;
@@ -242,8 +247,8 @@ hipError_t zero_ring(lbm_ctx* c) {
 
 // The graph of kGraphSteps steps from the current buffers and step parity,
 // with the previous step's partials pending (captured on first use).
-hipGraphExec_t graph_for(lbm_ctx* c) {
-    const int key = (c->cur == c->ws + c->L.A ? 0 : 2) + (int)(c->steps & 1);
+hipGraphExec_t graph_for(lbm_ctx* c, bool cached) {
+    const int key = (cached ? 4 : 0) + (c->cur == c->ws + c->L.A ? 0 : 2) + (int)(c->steps & 1);
     if (c->gexec[key]) return c->gexec[key];
     if (!c->cap_stream && hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) {
         c->cap_stream = nullptr;
@@ -255,7 +260,7 @@ hipGraphExec_t graph_for(lbm_ctx* c) {
     hipError_t he = hipSuccess;
     for (int k = 0; k < kGraphSteps && he == hipSuccess; ++k) {
         const int64_t t = c->steps + k;
-        he = step_raw(c, cur, nxt, c->partials[t & 1], c->partials[(t - 1) & 1], c->cap_stream, c->cached);
+        he = step_raw(c, cur, nxt, c->partials[t & 1], c->partials[(t - 1) & 1], c->cap_stream, cached);
         std::swap(cur, nxt);
     }
     hipGraph_t graph = nullptr;
@@ -283,7 +288,7 @@ size_t adjoint_bytes(const lbm_ctx* c) {
     return (size_t)(3 * 19 + 3) * 4 * c->np + index_bytes(c);
 }
 
-// The launch shape of a step: every block starts at once and walks the chunk
+// The launch shape of a step (its blocks here, its stores in choose): every block starts at once and walks the chunk
 // list with stride `grid`, so the chunks in flight form a window of `grid`
 // consecutive chunks.
 //
@@ -317,7 +322,6 @@ hipError_t choose_launch(lbm_ctx* c) {
     const size_t bytes = step_bytes(c);
     if (c->storage == LBM_F32 && chunks > cus * per_cu) per_cu = bytes <= kTwoBlockBytes ? std::min(per_cu, 2) : 1;
     c->grid = (int)std::min<int64_t>({chunks, cus * per_cu, (int64_t)kMaxGrid});
-    c->cached = bytes <= kCacheBytes && (c->storage == LBM_F32 || bytes >= kCacheLeast16);
     return hipSuccess;
 }
 
@@ -362,6 +366,71 @@ bool several_steps(lbm_ctx* c) {
         c->steps_fit = he == hipSuccess ? per_cu * std::max(c->cus, 1) : 0;
     }
     return chunks <= c->steps_fit;
+}
+
+// The live contexts, with what each has enqueued.
+std::mutex g_live_mu;
+lbm_ctx* g_live = nullptr;
+void live_add(lbm_ctx* c) {
+    std::lock_guard<std::mutex> lock(g_live_mu);
+    c->live_next = g_live;
+    if (g_live) g_live->live_prev = c;
+    g_live = c;
+}
+void live_remove(lbm_ctx* c) {
+    std::lock_guard<std::mutex> lock(g_live_mu);
+    if (c->live_prev) c->live_prev->live_next = c->live_next;
+    if (c->live_next) c->live_next->live_prev = c->live_prev;
+    if (g_live == c) g_live = c->live_next;
+}
+hipError_t drain(lbm_ctx* c) {
+    const hipError_t he = hipStreamSynchronize(c->stream);
+    if (he == hipSuccess) {
+        std::lock_guard<std::mutex> lock(g_live_mu);
+        c->taken_chunks = 0;
+        c->taken_bytes = 0;
+    }
+    return he;
+}
+
+// How the next n steps go, which work over `bytes` bytes, beside what contexts
+// on other streams have enqueued.  The results do not depend on it.
+//
+// Several steps a launch where the chunks of all small images fit the GPU at
+// once.  Single steps of several contexts overlap, while launches that do not
+// fit wait for each other (us per step over two and four contexts, single /
+// several: 880 chunks 8.3 / 11.3 and 7.0 / 12.3, 555 6.2 / 6.8 and 4.5 / 7.3).
+// Images of a third of the GPU or less take several while there is room beside
+// the launches of several steps (four contexts of 321 chunks, 1,024 fit: 3.0 us
+// with three of them so, 3.2 with none; of 427 chunks 3.9 with two, 3.8).
+//
+// Cached stores where what all of them work over fits the cache (128^3 pack,
+// 121 MB, cached / streaming: one context 26.5 / 28.8, two 21.3 / 23.6, four
+// 25.0 / 23.5).
+struct How {
+    bool several, cached;
+};
+How choose(lbm_ctx* c, int n, size_t bytes) {
+    const int64_t chunks = c->np / lbm::kChunk;
+    const bool small = n >= kStepsLeast && several_steps(c);
+    std::lock_guard<std::mutex> lock(g_live_mu);
+    int64_t other_chunks = 0, other_several = 0;
+    size_t other_bytes = 0;
+    for (const lbm_ctx* o = g_live; o; o = o->live_next) {
+        // one handle names a stream of every thread's own there
+        if (o == c || o->dev != c->dev || (o->stream == c->stream && c->stream != hipStreamPerThread)) continue;
+        other_chunks += o->taken_chunks;
+        if (o->taken_several) other_several += o->taken_chunks;
+        other_bytes += o->taken_bytes;
+    }
+    How how;
+    how.several = small && (chunks + other_chunks <= c->steps_fit ||
+                            (3 * chunks <= c->steps_fit && chunks + other_several <= c->steps_fit));
+    how.cached = bytes + other_bytes <= kCacheBytes && (c->storage == LBM_F32 || bytes >= kCacheLeast16);
+    c->taken_chunks = small ? chunks : 0;
+    c->taken_several = how.several;
+    c->taken_bytes = bytes;
+    return how;
 }
 
 int flush(lbm_ctx* c);
@@ -471,15 +540,16 @@ hipError_t one_step(lbm_ctx* c, const void* src, void* dst, bool cached) {
     return hipSuccess;
 }
 
-// Small images take several steps a launch (several_steps).  Otherwise step n
+// Small images take several steps a launch (choose).  Otherwise step n
 // (0-based) writes partials[n % 2]; its launch also reduces the partials of
 // step n-1 into the ring.  With a step pending, runs of kGraphSteps steps
 // replay a captured graph (one launch call instead of kGraphSteps; the
 // launches and their arguments are the same).
 int do_steps(lbm_ctx* c, int n) {
+    const How how = choose(c, n, step_bytes(c));
     int k = 0;
     while (k < n) {
-        if (n - k >= kStepsLeast && several_steps(c)) {
+        if (how.several && n - k >= kStepsLeast) {
             int rc = flush(c);
             if (rc) return rc;
             const int m = std::min(n - k, steps_per_launch(c));
@@ -490,7 +560,7 @@ int do_steps(lbm_ctx* c, int n) {
             continue;
         }
         if (c->graphs && c->pending && n - k >= kGraphSteps) {
-            hipGraphExec_t g = graph_for(c);
+            hipGraphExec_t g = graph_for(c, how.cached);
             if (g) {
                 HIP_TRY(hipGraphLaunch(g, c->stream));
                 c->steps += kGraphSteps;  // even: cur and nxt are back in place
@@ -499,7 +569,7 @@ int do_steps(lbm_ctx* c, int n) {
             }
             c->graphs = false;  // capture not available: plain launches from here on
         }
-        HIP_TRY(one_step(c, c->cur, c->nxt, c->cached));
+        HIP_TRY(one_step(c, c->cur, c->nxt, how.cached));
         std::swap(c->cur, c->nxt);
         ++k;
     }
@@ -519,7 +589,7 @@ int read_slot(lbm_ctx* c, int64_t step_index, double out[4]) {
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(out, c->ring + (step_index % kRing) * 4, 4 * sizeof(double),
                            hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(drain(c));
     return LBM_OK;
 }
 
@@ -648,6 +718,7 @@ const lbm_ctx* g_static_owner[kStaticDevices] = {};
 
 lbm_ctx::~lbm_ctx() {
     steps_unregister(this);
+    live_remove(this);
     for (auto& g : gexec)
         if (g) hipGraphExecDestroy(g);
     if (cap_stream) hipStreamDestroy(cap_stream);
@@ -815,6 +886,7 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
     if (he != hipSuccess) return cleanup(fail(LBM_EHIP, std::string("setup upload: ") + hipGetErrorString(he)));
     steps_register(c);
+    live_add(c);
     *ctx = c;
     return LBM_OK;
 }
@@ -908,7 +980,7 @@ int lbm_history(lbm_ctx* c, int count, double* u) {
     int rc = flush(c);
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(ring.data(), c->ring, ring.size() * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(drain(c));
     for (int t = 0; t < count; ++t) {
         const int64_t step = c->steps - count + t;
         for (int a = 0; a < 3; ++a) u[3 * t + a] = ring[(step % kRing) * 4 + a] / volume(c);
@@ -953,7 +1025,7 @@ int lbm_get_state(lbm_ctx* c, double* f) {
     const int S = kSlots;
     std::vector<char> raw(state_bytes(c->storage, c->np));
     HIP_TRY(hipMemcpyAsync(raw.data(), c->cur, raw.size(), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(drain(c));
     const double inv = 1.0 / std::ldexp(1.0, c->exponent);
     const _Float16* h16 = reinterpret_cast<const _Float16*>(raw.data());
     const _Float16* ref = h16 + (size_t)S * c->np;  // LBM_F16R: the reference array
@@ -996,7 +1068,7 @@ int lbm_get_state_nodes(lbm_ctx* c, const int64_t* nodes, int64_t count, double*
                 HIP_TRY(hipMemcpyAsync(rbuf.data(),
                                        static_cast<char*>(c->cur) + ((size_t)S * c->np + (size_t)q * lbm::kChunk) * es,
                                        lbm::kChunk * es, hipMemcpyDeviceToHost, c->stream));
-            HIP_TRY(hipStreamSynchronize(c->stream));
+            HIP_TRY(drain(c));
             loaded = q;
         }
         const int64_t m = n % lbm::kChunk;
@@ -1054,7 +1126,7 @@ int lbm_set_state(lbm_ctx* c, const double* f) {
     if (c->wall_mode == LBM_WALL_FULLWAY)  // the state one step older starts equal to it
         HIP_TRY(hipMemcpyAsync(c->nxt, c->cur, raw.size(), hipMemcpyDeviceToDevice, c->stream));
     HIP_TRY(zero_ring(c));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(drain(c));
     c->steps = 0;
     c->pending = false;
     return LBM_OK;
@@ -1165,7 +1237,7 @@ int lbm_set_symmetry(lbm_ctx* c, int mirror_y, int mirror_z) {
                            c->stream));
     HIP_TRY(hipMemcpyAsync(c->ws + c->L.count, bm.count.data(), bm.count.size() * 4, hipMemcpyHostToDevice,
                            c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(drain(c));
     c->idx.sym = sym;
     drop_graphs(c);
     return LBM_OK;
@@ -1306,12 +1378,13 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     // recomputed: fh^{last0+1} .. fh^{N-2} in the segment store, fh^{N-1} and
     // fh^N in the context's buffers.  (320^3 rock, 40 steps, a checkpoint every
     // 20: 27.7 -> 24.4 ms; 128^3 pack, 400 steps, every 40: 39.6 -> 38.7.)
-    const bool adj_cached = adjoint_bytes(c) <= kCacheBytes;
+    const bool cached = choose(c, 1, step_bytes(c)).cached;
+    How how = choose(c, N, adjoint_bytes(c));
     if (segs > 0) {
         const void* at = c->cur;
         for (int n = last0; n < nrev - 1;) {
             const int run = std::min(nrev - 1 - n, steps_per_launch(c));
-            if (run >= kStepsLeast && several_steps(c)) {
+            if (run >= kStepsLeast && how.several) {
                 int rc = flush(c);
                 if (rc) return rc;
                 HIP_TRY(run_steps(c, step_args(c, at, seg(n + 1 - last0), c->partials[0]), run, nullptr,
@@ -1319,19 +1392,20 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
                 c->steps += run;
                 n += run;
             } else {
-                HIP_TRY(one_step(c, at, seg(n + 1 - last0), adj_cached));
+                HIP_TRY(one_step(c, at, seg(n + 1 - last0), how.cached));
                 ++n;
             }
             at = seg(n - last0);
         }
         // fh^{N-1} and fh^N
-        HIP_TRY(one_step(c, at, c->nxt, c->cached));
-        HIP_TRY(one_step(c, c->nxt, c->cur, c->cached));
+        HIP_TRY(one_step(c, at, c->nxt, cached));
+        HIP_TRY(one_step(c, c->nxt, c->cur, cached));
     }
     HIP_TRY(timer.mark(kPhaseOther, c->stream));
     double u[3];
     int rc = lbm_mean_velocity(c, u);
     if (rc) return rc;
+    how = choose(c, N, adjoint_bytes(c));  // the reverse sweep's work
     const double gref = c->g[c->axis], V = volume(c), nu = viscosity(c);
     const double k = nu * u[c->axis] / gref;
 
@@ -1354,8 +1428,9 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     // stores and one from HBM (us per adjoint step, 1 / 2 blocks: 128^3 rock,
     // cached 63.1 / 58.3, streaming 64.3 / 62.5; 160^3, 206 MB, 103.2 / 100.5
     // and 103.8 / 104.3; 192^3, 350 MB, 168.5 / 171.0 and 162.7 / 165.8).
-    al.cached = adj_cached;
-    al.grid = (int)std::min<int64_t>(c->np / lbm::kChunk, (int64_t)std::max(c->cus, 1) * (al.cached ? 2 : 1));
+    al.cached = how.cached;
+    al.grid = (int)std::min<int64_t>(c->np / lbm::kChunk, (int64_t)std::max(c->cus, 1) *
+                                                              (adjoint_bytes(c) <= kCacheBytes ? 2 : 1));
     al.partials = part6;
     for (int s = segs - 1; s >= 0; --s) {
         const int n0 = s * K;                        // segment start: fh^{n0}
@@ -1365,7 +1440,7 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
         for (int t = 1; t < n1 - n0 && s < segs - 1;) {
             const void* src = t == 1 ? (const void*)snap(s) : (const void*)seg(t - 1);
             const int run = std::min(n1 - n0 - t, kStepsMost);
-            if (run >= kStepsLeast && several_steps(c)) {
+            if (run >= kStepsLeast && how.several) {
                 HIP_TRY(run_steps(c, step_args(c, src, seg(t), nullptr), run, nullptr, (int64_t)state));
                 t += run;
             } else {
@@ -1393,7 +1468,7 @@ int lbm_adjoint(lbm_ctx* c, int N, int K, void* workspace, size_t workspace_byte
     HIP_TRY(lbm::launch_finalize6(part6, al.grid, out6, c->stream));
     double cls[6];
     HIP_TRY(hipMemcpyAsync(cls, out6, sizeof(cls), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(drain(c));
     const lbm::RateClasses& dt = c->ds_dtau;
     const lbm::RateClasses& dl = c->ds_dLambda;
     const double via_t = cls[0] * dt.s_e + cls[1] * dt.s_eps + cls[2] * dt.s_q + cls[3] * dt.s_nu +

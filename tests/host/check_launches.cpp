@@ -1,0 +1,197 @@
+// Host logic of the C-ABI with the HIP runtime and the kernels replaced by
+// stand-ins that record what is launched, on which stream and how: which
+// contexts take several steps a launch and which stores their steps use while
+// contexts on other streams have work enqueued, and that no call names the
+// stream of another context.  No GPU.  Exit status 0 when every check holds.
+#include "lbm.h"
+#include "lbm_kernels.hpp"
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <set>
+#include <vector>
+
+namespace {
+std::set<hipStream_t> g_named;   // streams named by any call
+std::vector<hipStream_t> g_capturing;
+int g_single, g_several, g_graphs;
+std::vector<char> g_cached;      // stores of the single steps, captured ones too
+int g_fit = 4;                   // blocks of launch_steps per compute unit
+int g_bad = 0;
+
+void name(hipStream_t s) { g_named.insert(s); }
+void clear() {
+    g_named.clear();
+    g_single = g_several = g_graphs = 0;
+    g_cached.clear();
+}
+void check(bool ok, const char* what) {
+    if (!ok) {
+        std::printf("wrong: %s\n", what);
+        ++g_bad;
+    }
+}
+}  // namespace
+
+// ---------------------------------------------------------------- HIP runtime
+extern "C" {
+const char* hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+    name(st);
+    std::memmove(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) { name(s); return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    static uintptr_t next = 0x100000;
+    *s = reinterpret_cast<hipStream_t>(next += 16);
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
+    name(s);
+    *c = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
+    *g = reinterpret_cast<hipGraph_t>(0x10);
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+    static uintptr_t next = 0x200000;
+    *e = reinterpret_cast<hipGraphExec_t>(next += 16);
+    return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t s) { name(s); ++g_graphs; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) { name(s); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(0x30); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t s) { name(s); return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipErrorNotReady; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* t, hipEvent_t, hipEvent_t) { *t = 0.f; return hipSuccess; }
+}
+
+// -------------------------------------------------------------------- kernels
+namespace lbm {
+hipError_t static_scratch(void**) { return hipErrorInvalidValue; }
+hipError_t launch_step(const StepLaunch& a, hipStream_t s) {
+    name(s);
+    ++g_single;
+    g_cached.push_back(a.cached);
+    return hipSuccess;
+}
+hipError_t launch_steps(const StepLaunch&, int, void*, int64_t, uint32_t*, uint32_t*, hipStream_t s) {
+    name(s);
+    ++g_several;
+    return hipSuccess;
+}
+hipError_t steps_occupancy(const StepLaunch&, int* n) { *n = g_fit; return hipSuccess; }
+hipError_t step_occupancy(int, int, int, int* n) { *n = 5; return hipSuccess; }
+hipError_t launch_finalize(const double*, int, double*, uint32_t*, hipStream_t s) { name(s); return hipSuccess; }
+hipError_t launch_zero(void* p, int64_t n, hipStream_t s) { name(s); std::memset(p, 0, n); return hipSuccess; }
+hipError_t launch_rescale(int, void*, int64_t, float, hipStream_t s) { name(s); return hipSuccess; }
+hipError_t launch_adjoint_step(const AdjLaunch& a, hipStream_t s) { name(s); g_cached.push_back(a.cached); return hipSuccess; }
+hipError_t launch_fold(double*, const float*, int64_t, int64_t, hipStream_t s) { name(s); return hipSuccess; }
+hipError_t launch_adjoint_seed(float*, int64_t, int, float, hipStream_t s) { name(s); return hipSuccess; }
+hipError_t launch_finalize6(const double*, int, double*, hipStream_t s) { name(s); return hipSuccess; }
+hipError_t launch_add_uniform(double*, int64_t, double, double, double, hipStream_t s) { name(s); return hipSuccess; }
+}  // namespace lbm
+
+namespace {
+hipStream_t stream(int k) { return reinterpret_cast<hipStream_t>((uintptr_t)0x1000 * (k + 1)); }
+// a context of `chunks` full chunks on a stream
+struct Ctx {
+    lbm_ctx* c = nullptr;
+    void* ws = nullptr;
+    Ctx(int chunks, hipStream_t s, int storage = LBM_F32) {
+        const int nx = 256, ny = 16, nz = (chunks + 15) / 16;
+        std::vector<uint8_t> g((size_t)nx * ny * nz, 1);
+        std::fill(g.begin(), g.begin() + (size_t)chunks * 256, (uint8_t)0);
+        size_t bytes = 0;
+        check(lbm_workspace_query(g.data(), nx, ny, nz, storage, LBM_INDEX_BITMAP, &bytes, nullptr) == LBM_OK, "query");
+        ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+        const double f[3] = {1e-6, 0, 0};
+        check(lbm_setup(&c, g.data(), nx, ny, nz, 1.0, 3.0 / 16, LBM_SET_E, f, storage, LBM_INDEX_BITMAP, ws, bytes,
+                        s) == LBM_OK, "setup");
+    }
+    ~Ctx() {
+        lbm_destroy(c);
+        std::free(ws);
+    }
+    // what a call of 8 steps launched
+    bool several() {
+        clear();
+        lbm_step(c, 8);
+        check(g_several + g_single > 0, "launches");
+        return g_several > 0;
+    }
+    bool cached() {
+        clear();
+        lbm_step(c, 2);
+        return g_cached.back() != 0;
+    }
+    void drained() {
+        double u[3];
+        lbm_mean_velocity(c, u);
+    }
+};
+
+void several_contexts() {
+    Ctx a(600, stream(0)), b(600, stream(1)), d(340, stream(2)), e(600, stream(0)), h(350, stream(3));
+    check(a.several(), "one context takes several steps a launch");
+    check(a.several(), "and again");
+    check(!b.several(), "a second that does not fit beside it takes single steps");
+    check(!h.several(), "so does a third, of more than a third of the GPU");
+    check(d.several(), "one of less takes several beside the first");
+    h.drained();
+    check(!a.several(), "the first does not fit beside the others either");
+    check(!e.several(), "nor one on its stream");
+    b.drained();
+    check(e.several(), "but beside the smaller one alone");
+    e.drained();
+    a.drained();
+    check(b.several(), "the second does once the first's stream has been drained");
+    b.drained();
+    d.drained();
+    Ctx f(600, hipStreamPerThread), g(600, hipStreamPerThread);
+    check(f.several(), "a stream per thread");
+    check(!g.several(), "is another one in each thread");
+}
+
+void stores() {
+    // 4,000 chunks: 160 MB of FP32 states
+    Ctx a(4000, stream(0)), b(4000, stream(1));
+    check(a.cached(), "states inside the cache are stored there");
+    check(!b.cached(), "two contexts' states that do not fit it together are streamed");
+    check(!a.cached(), "by both");
+    b.drained();
+    check(a.cached(), "until the other's stream is drained");
+    // a replayed graph holds the stores it was captured with
+    clear();
+    lbm_step(a.c, 32);
+    check(g_graphs == 1 && g_cached.size() == 32 && g_cached.back(), "captured with cached stores");
+    b.cached();
+    clear();
+    lbm_step(a.c, 32);
+    check(g_graphs == 1 && g_cached.size() == 32 && !g_cached.back(), "captured again with streaming stores");
+    b.drained();
+    clear();
+    lbm_step(a.c, 32);
+    check(g_graphs == 1 && g_cached.empty(), "the first graph again");
+}
+}  // namespace
+
+int main() {
+    several_contexts();
+    stores();
+    std::printf("bad %d\n", g_bad);
+    return g_bad != 0;
+}
