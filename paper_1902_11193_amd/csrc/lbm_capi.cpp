@@ -7,10 +7,8 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
-#include <map>
 #include <mutex>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "lbm_host.hpp"
@@ -171,7 +169,6 @@ struct lbm_ctx {
     hipStream_t cap_stream;
     hipGraphExec_t gexec[8];
     int dev;           // the GPU of the workspace and stream
-    bool registered;   // counted in g_steps
     // what the work it has enqueued takes of the GPU (choose), until a call of
     // the library has seen its stream drained; in the list of live contexts
     int64_t taken_chunks;   // of small images
@@ -435,98 +432,9 @@ How choose(lbm_ctx* c, int n, size_t bytes) {
 
 int flush(lbm_ctx* c);
 
-// Launches of several steps need all their blocks running at once, so those of
-// different streams must fit the GPU together.  For every stream that a live
-// context works on: the share of the GPU its last such launch takes, and an
-// event recorded behind it.  With one stream (the usual case) nothing is
-// recorded, as its launches follow each other.  With more, a launch that does
-// not fit beside those still in flight waits, on the GPU, for the oldest of
-// them.  The kernel itself stays correct where it does not get its room
-// (k_steps).
-struct StepsInFlight {
-    int contexts = 0;
-    hipEvent_t event = nullptr;
-    double share = 0.0;
-    uint64_t launch = 0, waited = 0;   // its number, and that of the last launch that waits for it
-};
-std::mutex g_steps_mu;
-uint64_t g_launch = 1;
-// by device and stream; never destroyed, as contexts may outlive static objects
-auto& g_steps = *new std::map<std::pair<int, hipStream_t>, StepsInFlight>;
-
-// A second stream on the GPU: what the first has in flight was not recorded.
-void record_first(int dev) {
-    StepsInFlight* first = nullptr;
-    hipStream_t stream = nullptr;
-    for (auto& [key, s] : g_steps)
-        if (key.first == dev) {
-            if (first) return;  // more than one already
-            first = &s;
-            stream = key.second;
-        }
-    if (!first) return;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    hipError_t he = hipStreamIsCapturing(stream, &cap);
-    if (he == hipSuccess && cap != hipStreamCaptureStatusNone) return;
-    if (he == hipSuccess && !first->event) he = hipEventCreateWithFlags(&first->event, hipEventDisableTiming);
-    if (he == hipSuccess) he = hipEventRecord(first->event, stream);
-    if (he == hipSuccess)
-        first->share = 1.0;
-    else
-        (void)hipGetLastError();
-}
-void steps_register(lbm_ctx* c) {
-    std::lock_guard<std::mutex> lock(g_steps_mu);
-    if (!g_steps.count({c->dev, c->stream})) record_first(c->dev);
-    ++g_steps[{c->dev, c->stream}].contexts;
-    c->registered = true;
-}
-void steps_unregister(lbm_ctx* c) {
-    if (!c->registered) return;
-    std::lock_guard<std::mutex> lock(g_steps_mu);
-    const auto it = g_steps.find({c->dev, c->stream});
-    if (it == g_steps.end() || --it->second.contexts > 0) return;
-    if (it->second.event) hipEventDestroy(it->second.event);
-    g_steps.erase(it);
-}
-
 hipError_t run_steps(lbm_ctx* c, const lbm::StepLaunch& a, int steps, void* second, int64_t stride) {
-    uint32_t* sync = reinterpret_cast<uint32_t*>(c->ws + c->L.sync);
-    std::lock_guard<std::mutex> lock(g_steps_mu);
-    size_t streams = 0;
-    for (const auto& s : g_steps) streams += s.first.first == c->dev;
-    if (streams < 2) return lbm::launch_steps(a, steps, second, stride, sync, &c->told, c->stream);
-    StepsInFlight& mine = g_steps[{c->dev, c->stream}];
-    const double share = (double)(c->np / lbm::kChunk) / std::max(c->steps_fit, 1);
-    double others = 0.0;
-    for (auto& [key, s] : g_steps) {
-        if (key.first != c->dev || s.share == 0.0) continue;
-        if (hipEventQuery(s.event) == hipSuccess)
-            s.share = 0.0;
-        else
-            (void)hipGetLastError();  // not ready
-        if (&s != &mine) others += s.share;
-    }
-    hipError_t he = hipSuccess;
-    while (he == hipSuccess && others + share > 1.0) {  // behind the oldest, until the rest leaves room
-        StepsInFlight* oldest = nullptr;
-        for (auto& [key, s] : g_steps)
-            if (key.first == c->dev && &s != &mine && s.share > 0.0 && s.waited != g_launch &&
-                (!oldest || s.launch < oldest->launch))
-                oldest = &s;
-        if (!oldest) break;
-        he = hipStreamWaitEvent(c->stream, oldest->event, 0);
-        oldest->waited = g_launch;
-        others -= oldest->share;
-    }
-    if (he == hipSuccess && !mine.event) he = hipEventCreateWithFlags(&mine.event, hipEventDisableTiming);
-    if (he == hipSuccess) he = lbm::launch_steps(a, steps, second, stride, sync, &c->told, c->stream);
-    if (he == hipSuccess) he = hipEventRecord(mine.event, c->stream);
-    if (he == hipSuccess) {
-        mine.share = std::max(mine.share, share);
-        mine.launch = g_launch++;
-    }
-    return he;
+    return lbm::launch_steps(a, steps, second, stride, reinterpret_cast<uint32_t*>(c->ws + c->L.sync), &c->told,
+                             c->stream);
 }
 
 // One counted step from `src` to `dst`.
@@ -717,7 +625,6 @@ const lbm_ctx* g_static_owner[kStaticDevices] = {};
 }  // namespace
 
 lbm_ctx::~lbm_ctx() {
-    steps_unregister(this);
     live_remove(this);
     for (auto& g : gexec)
         if (g) hipGraphExecDestroy(g);
@@ -885,7 +792,6 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
     if (he == hipSuccess) he = zero_ring(c);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
     if (he != hipSuccess) return cleanup(fail(LBM_EHIP, std::string("setup upload: ") + hipGetErrorString(he)));
-    steps_register(c);
     live_add(c);
     *ctx = c;
     return LBM_OK;

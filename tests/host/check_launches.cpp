@@ -13,14 +13,16 @@
 #include <vector>
 
 namespace {
+constexpr uintptr_t kOwnStreams = 0x100000;
 std::set<hipStream_t> g_named;   // streams named by any call
-std::vector<hipStream_t> g_capturing;
-int g_single, g_several, g_graphs;
+int g_single, g_several, g_graphs, g_events;
 std::vector<char> g_cached;      // stores of the single steps, captured ones too
 int g_fit = 4;                   // blocks of launch_steps per compute unit
 int g_bad = 0;
 
-void name(hipStream_t s) { g_named.insert(s); }
+void name(hipStream_t s) {   // one that the library made to capture on aside
+    if (reinterpret_cast<uintptr_t>(s) < kOwnStreams) g_named.insert(s);
+}
 void clear() {
     g_named.clear();
     g_single = g_several = g_graphs = 0;
@@ -47,7 +49,7 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
 }
 hipError_t hipStreamSynchronize(hipStream_t s) { name(s); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
-    static uintptr_t next = 0x100000;
+    static uintptr_t next = kOwnStreams;
     *s = reinterpret_cast<hipStream_t>(next += 16);
     return hipSuccess;
 }
@@ -70,11 +72,15 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, c
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t s) { name(s); ++g_graphs; return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) { name(s); return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(0x30); return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) { name(s); ++g_events; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) {
+    ++g_events;
+    *e = reinterpret_cast<hipEvent_t>(0x30);
+    return hipSuccess;
+}
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t s) { name(s); return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t) { return hipErrorNotReady; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t s) { name(s); ++g_events; return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { ++g_events; return hipErrorNotReady; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* t, hipEvent_t, hipEvent_t) { *t = 0.f; return hipSuccess; }
 }
@@ -166,6 +172,27 @@ void several_contexts() {
     check(!g.several(), "is another one in each thread");
 }
 
+// A context's calls name no stream but its own, nor do they touch events: the
+// stream of an idle context may be gone, another thread may be capturing.
+void own_stream() {
+    Ctx a(600, stream(0));
+    lbm_step(a.c, 8);
+    a.drained();
+    clear();
+    g_events = 0;
+    {
+        Ctx b(300, stream(1)), d(1000, stream(1));
+        for (lbm_ctx* c : {b.c, d.c}) lbm_step(c, 40);
+        b.drained();
+        d.drained();
+    }
+    check(g_named == std::set<hipStream_t>{stream(1)}, "a context's calls stay on its stream");
+    Ctx b(300, stream(1));
+    for (int k = 0; k < 3; ++k)
+        for (lbm_ctx* c : {a.c, b.c}) lbm_step(c, 8);
+    check(g_events == 0, "no events");
+}
+
 void stores() {
     // 4,000 chunks: 160 MB of FP32 states
     Ctx a(4000, stream(0)), b(4000, stream(1));
@@ -190,6 +217,7 @@ void stores() {
 }  // namespace
 
 int main() {
+    own_stream();
     several_contexts();
     stores();
     std::printf("bad %d\n", g_bad);
