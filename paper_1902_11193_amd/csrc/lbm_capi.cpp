@@ -305,11 +305,23 @@ size_t adjoint_bytes(const lbm_ctx* c) {
 // the narrowest window keeps to the fewest DRAM pages (512^3 0.738 / 0.840 ms).
 constexpr size_t kCacheBytes = (size_t)256 << 20;
 constexpr size_t kTwoBlockBytes = (size_t)160 << 20;
-// 16-bit states of a few MB stay in L2 whole, and what is dirty there is
-// written back after the last block (FP16, us per step streaming / plain: a
-// rock of 1,407 chunks, 33 MB, 13.1 / 13.6, a bore of 1,649 chunks 14.2 /
-// 14.6; 192^3 rock, 122 MB, 35.4 / 30.9).
-constexpr size_t kCacheLeast16 = (size_t)48 << 20;
+// 16-bit states that fit the XCDs' 32 MB of L2, with their coordinates, stay
+// there, and what is dirty is written back after the last block: streaming
+// stores.  (Us per step streaming / plain, F16, BF16, F16R: rocks of 29 MiB 13.8
+// / 14.2, 13.8 / 14.0, 17.1 / 17.0, of 32 MiB 15.2 / 14.8, 15.3 / 14.5, 19.3 /
+// 18.2; packs of 29 MiB 13.9 / 14.3, 13.7 / 14.0, 18.1 / 17.6, of 33 MiB 15.8 /
+// 15.1, 15.9 / 14.9, 20.4 / 18.9; bores 16 voxels long of 31 MiB 14.3 / 14.8, 14.1
+// / 14.4, 18.7 / 18.6, of 38 MiB 16.1 / 16.1, 16.2 / 15.8, 21.5 / 20.3.)  Images a
+// few voxels long, whose gathers all fall close to the node, keep streaming
+// further (bores 4 voxels long of 38 MiB 15.9 / 16.4, 15.3 / 15.8, 20.3 / 19.9).
+constexpr size_t kCacheLeast16 = (size_t)32 << 20;
+constexpr int kShortRows = 8;
+constexpr size_t kCacheLeastShort = (size_t)48 << 20;
+bool past_l2(const lbm_ctx* c) {
+    if (c->storage == LBM_F32) return true;
+    if (c->nx < kShortRows) return step_bytes(c) >= kCacheLeastShort;
+    return 2 * state_bytes(c->storage, c->np) + 4 * (size_t)c->np >= kCacheLeast16;
+}
 hipError_t choose_launch(lbm_ctx* c) {
     int per_cu = 0;
     hipError_t he = lbm::step_occupancy(c->storage, c->index_kind, c->collision, &per_cu);
@@ -423,7 +435,7 @@ How choose(lbm_ctx* c, int n, size_t bytes) {
     How how;
     how.several = small && (chunks + other_chunks <= c->steps_fit ||
                             (3 * chunks <= c->steps_fit && chunks + other_several <= c->steps_fit));
-    how.cached = bytes + other_bytes <= kCacheBytes && (c->storage == LBM_F32 || bytes >= kCacheLeast16);
+    how.cached = bytes + other_bytes <= kCacheBytes && past_l2(c);
     c->taken_chunks = small ? chunks : 0;
     c->taken_several = how.several;
     c->taken_bytes = bytes;

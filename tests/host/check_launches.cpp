@@ -117,8 +117,8 @@ hipStream_t stream(int k) { return reinterpret_cast<hipStream_t>((uintptr_t)0x10
 struct Ctx {
     lbm_ctx* c = nullptr;
     void* ws = nullptr;
-    Ctx(int chunks, hipStream_t s, int storage = LBM_F32) {
-        const int nx = 256, ny = 16, nz = (chunks + 15) / 16;
+    Ctx(int chunks, hipStream_t s, int storage = LBM_F32, int nx = 256) {
+        const int ny = 4096 / nx, nz = (chunks + 15) / 16;
         std::vector<uint8_t> g((size_t)nx * ny * nz, 1);
         std::fill(g.begin(), g.begin() + (size_t)chunks * 256, (uint8_t)0);
         size_t bytes = 0;
@@ -214,12 +214,25 @@ void stores() {
     lbm_step(a.c, 32);
     check(g_graphs == 1 && g_cached.empty(), "the first graph again");
 }
+// 16-bit states: streaming stores while they fit the L2s.
+void small_states() {
+    for (int storage : {LBM_F16, LBM_BF16, LBM_F16R}) {
+        // 19.5 KB (F16R 20.5) per chunk and its coordinates
+        Ctx a(1500, stream(0), storage), b(1700, stream(0), storage), d(1700, stream(0), storage, 4);
+        check(!a.cached(), "states of 30 MB are streamed");
+        check(b.cached(), "states of 35 MB are stored in the caches");
+        check(!d.cached(), "but not with rows of four voxels");
+    }
+    Ctx e(1000, stream(0));
+    check(e.cached(), "FP32 states of any size are");
+}
 }  // namespace
 
 int main() {
     own_stream();
     several_contexts();
     stores();
+    small_states();
     std::printf("bad %d\n", g_bad);
     return g_bad != 0;
 }
