@@ -317,7 +317,8 @@ int lbm_set_collision(lbm_ctx* ctx, int collision);
  * lbm_wall_workspace_query bytes (256-byte aligned, caller-owned, must outlive
  * the mode).  The populations of one step earlier that it takes start equal to
  * the current state (as again after lbm_set_state); they are read from the
- * state buffer a step overwrites, so the workspace itself is not written.
+ * state buffer a step overwrites, so the workspace is a token 256 bytes that
+ * nothing reads or writes.
  * LBM_WALL_HALFWAY releases it (workspace may be NULL).  Errors: LBM_EINVAL
  * (unknown mode, storage other than FP32), LBM_EWORKSPACE.  lbm_adjoint refuses a
  * context in full-way mode. */

@@ -1085,9 +1085,15 @@ int lbm_set_collision(lbm_ctx* c, int collision) {
     return LBM_OK;
 }
 
+// Full-way walls need no memory of their own (the older state lies in the buffer
+// a step overwrites); callers still pass a workspace of the size they are told.
+namespace {
+constexpr size_t kWallBytes = 256;
+}
+
 int lbm_wall_workspace_query(lbm_ctx* c, size_t* bytes) {
     if (!c || !bytes) return fail(LBM_EINVAL, "NULL argument");
-    *bytes = align256((size_t)19 * c->np * 4);
+    *bytes = kWallBytes;
     return LBM_OK;
 }
 
@@ -1101,9 +1107,8 @@ int lbm_set_wall(lbm_ctx* c, int mode, void* workspace, size_t workspace_bytes) 
     if (mode != LBM_WALL_FULLWAY) return fail(LBM_EINVAL, "mode must be LBM_WALL_HALFWAY or LBM_WALL_FULLWAY");
     if (c->storage != LBM_F32) return fail(LBM_EINVAL, "full-way bounce-back needs FP32 storage");
     if (c->pressure) return fail(LBM_EINVAL, "full-way bounce-back cannot be combined with pressure faces");
-    const size_t need = align256((size_t)19 * c->np * 4);
     if (!workspace || ((uintptr_t)workspace & 255)) return fail(LBM_EWORKSPACE, "wall workspace NULL or not 256-byte aligned");
-    if (workspace_bytes < need) return fail(LBM_EWORKSPACE, "wall workspace too small: need " + std::to_string(need));
+    if (workspace_bytes < kWallBytes) return fail(LBM_EWORKSPACE, "wall workspace too small: need " + std::to_string(kWallBytes));
     // the state one step older than the current one starts equal to it; it is
     // read from the buffer the next step overwrites
     HIP_TRY(hipMemcpyAsync(c->nxt, c->cur, (size_t)19 * c->np * 4, hipMemcpyDeviceToDevice, c->stream));

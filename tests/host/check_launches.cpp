@@ -226,6 +226,17 @@ void small_states() {
     Ctx e(1000, stream(0));
     check(e.cached(), "FP32 states of any size are");
 }
+// Full-way walls hold no state of their own.
+void wall_workspace() {
+    Ctx a(1000, stream(0));
+    size_t bytes = 0;
+    check(lbm_wall_workspace_query(a.c, &bytes) == LBM_OK && bytes > 0 && bytes <= 4096, "a token workspace");
+    alignas(256) static char ws[8192];
+    check(bytes <= sizeof ws && lbm_set_wall(a.c, LBM_WALL_FULLWAY, ws, bytes) == LBM_OK, "of that size is accepted");
+    check(lbm_set_wall(a.c, LBM_WALL_FULLWAY, nullptr, bytes) == LBM_EWORKSPACE, "none is refused");
+    check(lbm_set_wall(a.c, LBM_WALL_FULLWAY, ws + 8, bytes) == LBM_EWORKSPACE, "a misaligned one too");
+    check(lbm_set_wall(a.c, LBM_WALL_FULLWAY, ws, bytes - 1) == LBM_EWORKSPACE, "and a smaller one");
+}
 }  // namespace
 
 int main() {
@@ -233,6 +244,7 @@ int main() {
     several_contexts();
     stores();
     small_states();
+    wall_workspace();
     std::printf("bad %d\n", g_bad);
     return g_bad != 0;
 }
