@@ -226,6 +226,49 @@ void small_states() {
     Ctx e(1000, stream(0));
     check(e.cached(), "FP32 states of any size are");
 }
+// Replayed graphs of larger images: captured on first use, again after any
+// change of what their launches bake in, and not by launches of several steps.
+void graphs() {
+    Ctx a(1000, stream(0));
+    int steps = 0;
+    // graph replays and single launches (captured ones too) of n steps
+    auto run = [&](int n, int replays, int singles) {
+        clear();
+        steps += n;
+        return lbm_step(a.c, n) == LBM_OK && g_several == 0 && g_graphs == replays && g_single == singles;
+    };
+    check(run(1, 0, 1), "a first step");
+    check(run(65, 2, 33), "one capture, two replays, a single step");
+    check(run(64, 2, 32), "an odd start is captured apart");
+    check(run(64, 2, 0), "then replayed only");
+    const auto fresh = [&](const char* what) {
+        check(run(32, 1, 32), what);
+        check(run(32, 1, 0), "and replayed");
+    };
+    static float field[3 * 256 * 1000];
+    alignas(256) static char ws[256];
+    lbm_set_collision(a.c, LBM_COLLIDE_TRT);
+    check(run(1, 0, 1), "nothing pending after a change of collision");
+    fresh("captured after a change of collision");
+    lbm_set_force_field(a.c, field);
+    fresh("after a force field");
+    lbm_set_wall(a.c, LBM_WALL_FULLWAY, ws, 256);
+    fresh("after full-way walls");
+    lbm_set_symmetry(a.c, 1, 0);
+    fresh("after symmetry planes");
+    lbm_set_symmetry(a.c, 0, 0);
+    lbm_set_wall(a.c, LBM_WALL_HALFWAY, nullptr, 0);
+    fresh("after halfway walls");
+    lbm_set_graphs(a.c, 0);
+    check(run(64, 0, 64), "plain launches on request");
+    Ctx b(1000, stream(0), LBM_F16);
+    lbm_step(b.c, 33);
+    lbm_set_storage_exponent(b.c, 9);
+    clear();
+    lbm_step(b.c, 32);
+    check(g_graphs == 1 && g_single == 32, "after a change of the storage exponent");
+}
+
 // Full-way walls hold no state of their own.
 void wall_workspace() {
     Ctx a(1000, stream(0));
@@ -244,6 +287,7 @@ int main() {
     several_contexts();
     stores();
     small_states();
+    graphs();
     wall_workspace();
     std::printf("bad %d\n", g_bad);
     return g_bad != 0;
