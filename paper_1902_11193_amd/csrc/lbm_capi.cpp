@@ -285,9 +285,13 @@ size_t adjoint_bytes(const lbm_ctx* c) {
     return (size_t)(3 * 19 + 3) * 4 * c->np + index_bytes(c);
 }
 
-// The launch shape of a step (its blocks here, its stores in choose): every block starts at once and walks the chunk
-// list with stride `grid`, so the chunks in flight form a window of `grid`
-// consecutive chunks.
+// The launch shape of a step: its blocks (here) and its stores (choose).  A
+// block walks the chunk list with stride `grid`, so the chunks in flight form a
+// window of at most `grid` consecutive chunks.  The blocks that fit a compute
+// unit are asked of the plain kernel of the storage, index and collision, as
+// the block sums are to be grouped alike in every setting; of the variants with
+// more registers (full-way walls with mirror planes: 3 blocks of the TRT
+// collision instead of 5) a few blocks may start later.
 //
 // Stores: where all a step goes over fits the 256 MB cache behind L2, plain
 // stores leave the results there for the next step; past it they only push
@@ -397,6 +401,7 @@ hipError_t drain(lbm_ctx* c) {
     if (he == hipSuccess) {
         std::lock_guard<std::mutex> lock(g_live_mu);
         c->taken_chunks = 0;
+        c->taken_several = false;
         c->taken_bytes = 0;
     }
     return he;
@@ -436,9 +441,10 @@ How choose(lbm_ctx* c, int n, size_t bytes) {
     how.several = small && (chunks + other_chunks <= c->steps_fit ||
                             (3 * chunks <= c->steps_fit && chunks + other_several <= c->steps_fit));
     how.cached = bytes + other_bytes <= kCacheBytes && past_l2(c);
-    c->taken_chunks = small ? chunks : 0;
-    c->taken_several = how.several;
-    c->taken_bytes = bytes;
+    // earlier calls' work may still run
+    if (small) c->taken_chunks = chunks;
+    c->taken_several |= how.several;
+    c->taken_bytes = std::max(c->taken_bytes, bytes);
     return how;
 }
 

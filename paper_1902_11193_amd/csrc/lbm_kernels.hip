@@ -171,7 +171,7 @@ __device__ __forceinline__ void st_stream(T* base, uint32_t byte_off, T v) {
 
 // Store of a node's result: CACHED where the states fit the caches (the next
 // step reads them there), else streaming.  Which of the two a launch takes
-// follows from the size of the states (kCachedBytes).
+// follows from the size of the states (StepLaunch::cached).
 template <bool CACHED, class T>
 __device__ __forceinline__ void st_state(T* base, uint32_t byte_off, T v) {
     if constexpr (CACHED)

@@ -167,6 +167,11 @@ void several_contexts() {
     check(b.several(), "the second does once the first's stream has been drained");
     b.drained();
     d.drained();
+    check(a.several(), "the first again");
+    lbm_step(a.c, 1);
+    check(!b.several(), "a single step behind launches of several hides nothing");
+    a.drained();
+    b.drained();
     Ctx f(600, hipStreamPerThread), g(600, hipStreamPerThread);
     check(f.several(), "a stream per thread");
     check(!g.several(), "is another one in each thread");
