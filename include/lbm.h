@@ -359,7 +359,9 @@ int lbm_set_symmetry(lbm_ctx* ctx, int mirror_y, int mirror_z);
  * step is pending, by replaying a HIP graph captured from the same launches on
  * first use.  The results are identical to one launch a step, which enable = 0
  * selects.  A launch of several steps that does not get the whole of the GPU it
- * needs within 0.1 ms, because other work holds it, goes on with what it gets.
+ * needs within 0.1 ms, because other work holds it, goes on with what it gets;
+ * once lbm_history or lbm_run_to_steady has seen that, the next calls take
+ * single steps.
  * Any change of collision, wall, pressure, force field or storage
  * exponent drops the captured graphs. */
 int lbm_set_graphs(lbm_ctx* ctx, int enable);

@@ -87,8 +87,8 @@ Layout layout(int64_t np, int64_t nf, int storage, int index_kind, int nx, int n
     // contexts keep it in the static array instead)
     L.partials = off;  // two buffers: steps alternate between them
     off += 2 * lbm::kPartialBytes;
-    L.ring = off;  // ring of per-step sums, then the device counter of steps reduced
-    off += align256((size_t)kRing * 4 * 8 + sizeof(uint32_t));
+    L.ring = off;  // ring of per-step sums, then the device counters
+    off += align256(lbm::kRingBytes);
     L.total = off;
     return L;
 }
@@ -155,6 +155,12 @@ struct lbm_ctx {
     int grid;
     int steps_fit;  // blocks of launch_steps that run at once with the current settings; -1: not asked yet
     uint32_t told;  // what launch_steps has the chunks' words hold
+    // launches of several steps whose blocks did not all meet, as last read;
+    // whether there were such launches since; calls that take single steps for
+    // it, of how many
+    uint32_t closed;
+    bool several_since;
+    int apart, apart_of;
     double* partials[2];
     double* ring;
     uint32_t* ctr;      // steps reduced into the ring so far (device, after the ring)
@@ -239,7 +245,8 @@ void drop_graphs(lbm_ctx* c) {
 }
 
 hipError_t zero_ring(lbm_ctx* c) {
-    return lbm::launch_zero(c->ring, (int64_t)kRing * 4 * 8 + (int64_t)sizeof(uint32_t), c->stream);
+    c->closed = 0;
+    return lbm::launch_zero(c->ring, (int64_t)lbm::kRingBytes, c->stream);
 }
 
 // The graph of kGraphSteps steps from the current buffers and step parity,
@@ -407,6 +414,20 @@ hipError_t drain(lbm_ctx* c) {
     return he;
 }
 
+// Where other work (another process, other kernels) keeps blocks of a launch of
+// several steps from meeting, the context goes on with single steps for 8
+// calls, twice as many each time it is so again (two processes of 800 chunks,
+// us per step of each: 25.7 with such launches all the time, 16 so).
+constexpr int kApartFirst = 8, kApartMost = 256;
+void look_at_closed(lbm_ctx* c, uint32_t closed) {
+    if (closed != c->closed)
+        c->apart = c->apart_of = std::min(std::max(2 * c->apart_of, kApartFirst), kApartMost);
+    else if (c->several_since)
+        c->apart_of = 0;
+    c->closed = closed;
+    c->several_since = false;
+}
+
 // How the next n steps go, which work over `bytes` bytes, beside what contexts
 // on other streams have enqueued.  The results do not depend on it.
 //
@@ -438,12 +459,15 @@ How choose(lbm_ctx* c, int n, size_t bytes) {
         other_bytes += o->taken_bytes;
     }
     How how;
-    how.several = small && (chunks + other_chunks <= c->steps_fit ||
+    const bool apart = small && c->apart > 0;
+    if (apart) --c->apart;
+    how.several = small && !apart && (chunks + other_chunks <= c->steps_fit ||
                             (3 * chunks <= c->steps_fit && chunks + other_several <= c->steps_fit));
     how.cached = bytes + other_bytes <= kCacheBytes && past_l2(c);
     // earlier calls' work may still run
     if (small) c->taken_chunks = chunks;
     c->taken_several |= how.several;
+    c->several_since |= how.several;
     c->taken_bytes = std::max(c->taken_bytes, bytes);
     return how;
 }
@@ -726,6 +750,9 @@ int setup_impl(lbm_ctx** ctx, const uint8_t* geometry, int nx, int ny, int nz, d
     c->graphs = true;
     c->steps_fit = -1;
     c->told = 0;
+    c->closed = 0;
+    c->several_since = false;
+    c->apart = c->apart_of = 0;
     c->cap_stream = nullptr;
     for (auto& g : c->gexec) g = nullptr;
     c->steps = 0;
@@ -900,11 +927,15 @@ int lbm_history(lbm_ctx* c, int count, double* u) {
     if (!c || !u) return fail(LBM_EINVAL, "NULL argument");
     if (count < 0 || count > kRing || count > c->steps)
         return fail(LBM_EINVAL, "count must be in [0, min(1024, steps done)]");
-    std::vector<double> ring((size_t)kRing * 4);
+    static_assert(lbm::kRingBytes == ((size_t)kRing * 4 + 1) * 8, "the counters follow the ring");
+    std::vector<double> ring((size_t)kRing * 4 + 1);
     int rc = flush(c);
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(ring.data(), c->ring, ring.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipMemcpyAsync(ring.data(), c->ring, lbm::kRingBytes, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(drain(c));
+    uint32_t counters[2];
+    std::memcpy(counters, &ring[(size_t)kRing * 4], sizeof(counters));
+    look_at_closed(c, counters[1]);
     for (int t = 0; t < count; ++t) {
         const int64_t step = c->steps - count + t;
         for (int a = 0; a < 3; ++a) u[3 * t + a] = ring[(step % kRing) * 4 + a] / volume(c);

@@ -1240,10 +1240,10 @@ constexpr uint32_t kClosed = 0x80000000u;   // sync[0]: the count is closed
 constexpr int64_t kMeetTicks = 10000;       // 0.1 ms of the 100 MHz clock
 constexpr int64_t kStuckTicks = 2000000000; // 20 s: no block came (a lost GPU); sums become NaN
 // Words of sync: the count, blocks that left a closed count, kMeetTicks where
-// set (kNever: the count is closed from the start), closed counts so far, a
-// block waited in vain; on a line of its own the next chunk-step.
+// set (kNever: the count is closed from the start), a block waited in vain; on
+// a line of its own the next chunk-step.  ctr[1] counts the closed counts.
 constexpr uint32_t kNever = 0xffffffffu;
-constexpr uint32_t kLeft = 1, kMeetWord = 2, kClosedSoFar = 3, kLost = 4, kNext = 16;
+constexpr uint32_t kLeft = 1, kMeetWord = 2, kLost = 4, kNext = 16;
 
 __device__ __forceinline__ uint32_t ld_sync(const uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1255,11 +1255,11 @@ __device__ __forceinline__ uint32_t add_sync(uint32_t* p) {
     return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Thread 0 of a block counts it in.  False: the count is closed.
-__device__ __forceinline__ bool count_in(uint32_t* sync, uint32_t blocks) {
+__device__ __forceinline__ bool count_in(uint32_t* sync, uint32_t* closed, uint32_t blocks) {
     const uint32_t set = ld_sync(sync + kMeetWord);
     uint32_t v = add_sync(sync) + 1u;
     if (set == kNever) {
-        if (v == 1u) add_sync(sync + kClosedSoFar);
+        if (v == 1u) add_sync(closed);
         return false;
     }
     const int64_t most = set ? (int64_t)set : kMeetTicks, t0 = wall_clock64();
@@ -1268,7 +1268,7 @@ __device__ __forceinline__ bool count_in(uint32_t* sync, uint32_t blocks) {
             v = ld_sync(sync);
         } else if (__hip_atomic_compare_exchange_strong(sync, &v, v | kClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_AGENT)) {
-            add_sync(sync + kClosedSoFar);
+            add_sync(closed);
             return false;
         }  // else v holds the count as it is now
     }
@@ -1290,7 +1290,7 @@ k_steps(const StepsArgs a, Ix ix) {
     auto done = [&](uint32_t q) { return a.sync + kSyncHead + q * kSyncStride; };
     if (threadIdx.x == 0) {
         s_stuck = false;
-        s_word = count_in(a.sync, G);
+        s_word = count_in(a.sync, a.ctr + 1, G);
     }
     __syncthreads();
     const bool together = s_word != 0u;

@@ -16,11 +16,13 @@ constexpr uint32_t kRingSlots = 1024;
 // Most blocks a step launch uses (its per-block partial sums are sized for it).
 constexpr int kMaxGrid = 8192;
 // The reduction scratch of a context: two buffers of per-block partial sums
-// (double[kMaxGrid][4] each, 256-byte aligned) and the ring with its step
-// counter, in that order; the tail of a workspace, or the static array.
+// (double[kMaxGrid][4] each, 256-byte aligned) and the ring with its two
+// counters (StepLaunch::ctr), in that order; the tail of a workspace, or the
+// static array.
 constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 constexpr size_t kPartialBytes = align256((size_t)kMaxGrid * 4 * 8);
-constexpr size_t kReductionBytes = 2 * kPartialBytes + align256((size_t)kRingSlots * 4 * 8 + 4);
+constexpr size_t kRingBytes = (size_t)kRingSlots * 4 * 8 + 2 * 4;
+constexpr size_t kReductionBytes = 2 * kPartialBytes + align256(kRingBytes);
 
 // Device address of the current GPU's static reduction scratch (one array
 // of kReductionBytes per GPU, kept until the process ends), looked up once
@@ -63,7 +65,8 @@ struct StepLaunch {
     const double* prev_partials;  // [grid][4] of the previous step, reduced by block 0 into
                                   // ring slot (*ctr % kRingSlots), then ++*ctr; nullptr: nothing pending
     double* ring;                 // [kRingSlots][4] per-step sums
-    uint32_t* ctr;                // steps reduced so far (device)
+    uint32_t* ctr;                // steps reduced so far (device); behind it, launches of launch_steps whose
+                                  // blocks did not all meet
     bool fullway;         // full-way bounce-back (FP32 storage only): dst holds the state one step older than src
     bool pressure;        // Zou-He pressure faces at x = 0 and x = nx - 1 (FP32, bitmap, no field)
     float drho_in, drho_out;  // their density deviations rho - rho0

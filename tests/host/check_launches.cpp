@@ -18,6 +18,7 @@ std::set<hipStream_t> g_named;   // streams named by any call
 int g_single, g_several, g_graphs, g_events;
 std::vector<char> g_cached;      // stores of the single steps, captured ones too
 int g_fit = 4;                   // blocks of launch_steps per compute unit
+bool g_crowded;                  // the blocks of launch_steps do not meet
 int g_bad = 0;
 
 void name(hipStream_t s) {   // one that the library made to capture on aside
@@ -94,9 +95,10 @@ hipError_t launch_step(const StepLaunch& a, hipStream_t s) {
     g_cached.push_back(a.cached);
     return hipSuccess;
 }
-hipError_t launch_steps(const StepLaunch&, int, void*, int64_t, uint32_t*, uint32_t*, hipStream_t s) {
+hipError_t launch_steps(const StepLaunch& a, int, void*, int64_t, uint32_t*, uint32_t*, hipStream_t s) {
     name(s);
     ++g_several;
+    if (g_crowded) ++a.ctr[1];
     return hipSuccess;
 }
 hipError_t steps_occupancy(const StepLaunch&, int* n) { *n = g_fit; return hipSuccess; }
@@ -274,6 +276,31 @@ void graphs() {
     check(g_graphs == 1 && g_single == 32, "after a change of the storage exponent");
 }
 
+// After a launch whose blocks did not meet: single steps for 8 calls, then 16,
+// ..., and several a launch again once they do.
+void crowded_gpu() {
+    Ctx a(600, stream(0));
+    double u[3];
+    auto call = [&] {
+        const bool s = a.several();
+        lbm_history(a.c, 1, u);
+        return s;
+    };
+    check(call() && call(), "several steps a launch");
+    for (int apart : {8, 16, 32}) {
+        g_crowded = true;
+        check(call(), "a launch that did not meet");
+        g_crowded = false;
+        for (int k = 0; k < apart; ++k) check(!call(), "single steps for a while");
+    }
+    check(call() && call(), "several again");
+    g_crowded = true;
+    check(call(), "another time");
+    g_crowded = false;
+    for (int k = 0; k < 8; ++k) check(!call(), "the wait starts small again");
+    check(call(), "and ends");
+}
+
 // Full-way walls hold no state of their own.
 void wall_workspace() {
     Ctx a(1000, stream(0));
@@ -293,6 +320,7 @@ int main() {
     stores();
     small_states();
     graphs();
+    crowded_gpu();
     wall_workspace();
     std::printf("bad %d\n", g_bad);
     return g_bad != 0;
