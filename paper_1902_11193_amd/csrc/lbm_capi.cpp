@@ -434,10 +434,10 @@ void look_at_closed(lbm_ctx* c, uint32_t closed) {
 // Several steps a launch where the chunks of all small images fit the GPU at
 // once.  Single steps of several contexts overlap, while launches that do not
 // fit wait for each other (us per step over two and four contexts, single /
-// several: 880 chunks 8.3 / 11.3 and 7.0 / 12.3, 555 6.2 / 6.8 and 4.5 / 7.3).
+// several: 880 chunks 8.3 / 11.3 and 7.0 / 12.3, four of 555 4.5 / 7.3).
 // Images of a third of the GPU or less take several while there is room beside
-// the launches of several steps (four contexts of 321 chunks, 1,024 fit: 3.0 us
-// with three of them so, 3.2 with none; of 427 chunks 3.9 with two, 3.8).
+// the launches of several steps (four contexts of 321 chunks, 1,280 fit: 2.9 us
+// with three of them so, 3.2 with none).
 //
 // Cached stores where what all of them work over fits the cache (128^3 pack,
 // 121 MB, cached / streaming: one context 26.5 / 28.8, two 21.3 / 23.6, four

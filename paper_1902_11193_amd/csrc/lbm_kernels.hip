@@ -1275,8 +1275,12 @@ __device__ __forceinline__ bool count_in(uint32_t* sync, uint32_t* closed, uint3
     return !(v & kClosed);
 }
 
+// 96 VGPRs without spilling, so that 5 blocks fit a CU, except in the variants
+// that k_step leaves to the compiler too: what fits decides how many contexts
+// take such launches at once (four of a 272-chunk channel, 16,000 steps in all:
+// 48 ms with 4 blocks per CU, 41 with 5).
 template <class C, class Ix, bool FIELD, bool TRT, bool FW, bool ZH, bool SYM>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, (C::kRef || FW || SYM) ? 1 : 5)
 k_steps(const StepsArgs a, Ix ix) {
     using T = typename C::T;
     constexpr int S = C::kSlots;
