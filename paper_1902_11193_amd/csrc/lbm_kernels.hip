@@ -1204,7 +1204,7 @@ k_step(const typename C::T* __restrict__ src, typename C::T* __restrict__ dst, I
 // after the last one, in the order the single-step launches use (the same
 // results bit for bit).  Measured, one launch a step -> here, us per step: the
 // 13 chunks of a bore 32 voxels wide 6.0 -> 3.3, the 32^3 sphere array, 120
-// chunks, 6.7 -> 3.8, the 202 chunks of a bore 128 voxels wide 6.6 -> 3.7.  What
+// chunks, 6.7 -> 3.9, the 202 chunks of a bore 128 voxels wide 6.6 -> 3.8.  What
 // is left is the way of a value between blocks: store, its acknowledgement,
 // the word, the poll that sees it, the gather, and 0.5 us of arithmetic.
 //
